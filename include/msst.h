@@ -428,8 +428,7 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
  * minus half a voxel diagonal.  1..256 primitives, res <= 4096.  For a mesh
  * scene (n_tris > 0, tris on the device) the distance is the FP64 distance
  * to the nearest triangle, negative where a ray from the voxel centre along
- * (1, 2, 3) / sqrt(14) crosses the mesh an odd number of times (every
- * triangle is tested: a pre-process, not a per-frame cost). */
+ * (1, 2, 3) / sqrt(14) crosses the mesh an odd number of times. */
 ms_status ms_build_sdf_grid(const ms_scene* scene, int32_t res, uint16_t* grid_dev, void* stream);
 
 /* FP64 image statistics (deterministic): out_dev[0] mean radiance,

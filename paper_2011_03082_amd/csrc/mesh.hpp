@@ -149,4 +149,23 @@ __device__ inline bool tri_ray_crosses64(const float* tr, const double* p, const
     return dot3(e2, qv) * inv > 0.0;
 }
 
+// binary16 bits of x rounded toward zero.
+__device__ __forceinline__ uint16_t fp16_bits_rtz(double x) {
+    const uint16_t sign = x < 0.0 ? 0x8000u : 0u;
+    const double a = fabs(x);
+    if (a >= 65504.0) return (uint16_t)(sign | 0x7bffu);
+    if (a < 0x1p-24) return sign;
+    int e;
+    frexp(a, &e);
+    const int ex = e - 1;  // a in [2^ex, 2^(ex+1))
+    if (ex < -14) return (uint16_t)(sign | (uint32_t)floor(a * 0x1p24));
+    const uint32_t mant = (uint32_t)floor((ldexp(a, -ex) - 1.0) * 1024.0);
+    return (uint16_t)(sign | ((uint32_t)(ex + 15) << 10) | mant);
+}
+
+// Queues the distance grid of a mesh (mesh.hip): res^3 voxels of size h from
+// corner lo.
+void launch_mesh_grid(const float* tris, int n_tris, int res, const float* lo, const double* h, uint16_t* grid,
+                      int cus, hipStream_t stream);
+
 }  // namespace msst

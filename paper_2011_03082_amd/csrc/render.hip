@@ -1308,19 +1308,6 @@ __device__ __forceinline__ double prim_sdf64(const float* pr, double px, double 
     return sqrt(ox * ox + oy * oy + oz * oz) + fmin(fmax(ex, fmax(ey, ez)), 0.0);
 }
 
-__device__ __forceinline__ uint16_t fp16_bits_rtz(double x) {
-    const uint16_t sign = x < 0.0 ? 0x8000u : 0u;
-    const double a = fabs(x);
-    if (a >= 65504.0) return (uint16_t)(sign | 0x7bffu);
-    if (a < 0x1p-24) return sign;
-    int e;
-    frexp(a, &e);
-    const int ex = e - 1;  // a in [2^ex, 2^(ex+1))
-    if (ex < -14) return (uint16_t)(sign | (uint32_t)floor(a * 0x1p24));
-    const uint32_t mant = (uint32_t)floor((ldexp(a, -ex) - 1.0) * 1024.0);
-    return (uint16_t)(sign | ((uint32_t)(ex + 15) << 10) | mant);
-}
-
 __global__ void sdf_grid_kernel(const float* prims, int n_prims, int res, double lox, double loy, double loz,
                                 double hx, double hy, double hz, uint16_t* out) {
     const int64_t total = (int64_t)res * res * res;
@@ -1330,26 +1317,6 @@ __global__ void sdf_grid_kernel(const float* prims, int n_prims, int res, double
         double sd = INFINITY;
         for (int q = 0; q < n_prims; ++q) sd = fmin(sd, prim_sdf64(prims + 8 * q, px, py, pz));
         out[v] = fp16_bits_rtz(sd);
-    }
-}
-
-// Mesh bodies: distance to the nearest triangle, negative where the ray from
-// the voxel centre along (1, 2, 3) / sqrt(14) crosses the mesh an odd number
-// of times.  Every triangle is visited (a pre-process).
-__global__ void sdf_grid_mesh_kernel(const float* tris, int n_tris, int res, double lox, double loy, double loz,
-                                     double hx, double hy, double hz, uint16_t* out) {
-    const double u[3] = {0.2672612419124244, 0.5345224838248488, 0.8017837257372732};
-    const int64_t total = (int64_t)res * res * res;
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < total; v += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = v % res, j = (v / res) % res, k = v / ((int64_t)res * res);
-        const double p[3] = {lox + (i + 0.5) * hx, loy + (j + 0.5) * hy, loz + (k + 0.5) * hz};
-        double dmin = INFINITY;
-        int odd = 0;
-        for (int q = 0; q < n_tris; ++q) {
-            dmin = fmin(dmin, tri_distance64(tris + 9 * q, p));
-            odd ^= (int)tri_ray_crosses64(tris + 9 * q, p, u);
-        }
-        out[v] = fp16_bits_rtz(odd ? -dmin : dmin);
     }
 }
 
@@ -1579,9 +1546,7 @@ extern "C" ms_status ms_build_sdf_grid(const ms_scene* scene, int32_t res, uint1
     const double h[3] = {((double)scene->hi[0] - scene->lo[0]) / res, ((double)scene->hi[1] - scene->lo[1]) / res,
                          ((double)scene->hi[2] - scene->lo[2]) / res};
     if (mesh)
-        hipLaunchKernelGGL(sdf_grid_mesh_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, scene->tris,
-                           scene->n_tris, res, (double)scene->lo[0], (double)scene->lo[1], (double)scene->lo[2], h[0],
-                           h[1], h[2], grid_dev);
+        launch_mesh_grid(scene->tris, scene->n_tris, res, scene->lo, h, grid_dev, cus, (hipStream_t)stream);
     else
         hipLaunchKernelGGL(sdf_grid_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, scene->prims,
                            scene->n_prims, res, (double)scene->lo[0], (double)scene->lo[1], (double)scene->lo[2], h[0],

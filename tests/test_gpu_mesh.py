@@ -63,3 +63,32 @@ def test_mesh_render_path_by_path(msst, oracle, blob, method, sampler):
     assert frac < 2e-3
     if method == ST:
         assert o["steps"].sum() > 50
+
+
+def thin_triangles(seed, n):
+    """An open soup of triangles, a third of them needles and a seventh
+    without area: no filter may drop one, nor take a bound from one."""
+    rng = np.random.default_rng(seed)
+    t = (0.4 * rng.normal(size=(n, 9))).astype(np.float32)
+    t[::3, 6:9] = t[::3, 3:6] + (1e-6 * rng.normal(size=t[::3, 3:6].shape)).astype(np.float32)
+    t[::7, 3:6] = t[::7, 0:3]
+    return t
+
+
+@pytest.mark.parametrize("name,res", [("coarse", 1), ("coarse", 5), ("fine", 9), ("fine", 16), ("thin", 18),
+                                      ("one", 7), ("many", 6)])
+def test_mesh_grid_culling_matches_oracle(msst, oracle, name, res):
+    """The grid at the edges of its bricks (sizes around multiples of four),
+    with lists of one part (80 triangles) and of several (20 480 triangles,
+    all kept around the centre; 6 000 overlapping needles), one triangle, and
+    triangles too thin for FP32.  Both sides evaluate the same FP64 distance
+    and crossing of every triangle that matters, so a voxel differs only where
+    the two compilers' FP64 rounding (1e-16 relative) straddles a binary16
+    step (1e-3): none of these few thousand is expected to."""
+    announce(f"mesh sdf grid culling {name} res={res}")
+    tris = {"coarse": lambda: W.mesh_blob(1, 1), "fine": lambda: W.mesh_blob(2, 5),
+            "thin": lambda: thin_triangles(3, 300), "one": lambda: W.mesh_blob(0, 0)[:1],
+            "many": lambda: thin_triangles(4, 6000)}[name]()
+    g = msst.build_sdf_grid(None, res, LO, HI, tris=tris).cpu().numpy().view(np.uint16)
+    o = oracle.Scene(None, tris=tris).build_grid(res, LO, HI)
+    assert np.array_equal(g, o), (int((g != o).sum()), g.size)
