@@ -90,7 +90,7 @@ struct Prims {
 struct RenderLds {
     float x[64][kTile];  // decoder input rows of the compacted lanes; outputs overwrite them
     float eps[64][6];    // decoder posterior noise of each row (at most 6 outputs)
-    uint4 rid[64];       // Philox stream (id_lo, id_hi) and first block of each row's normals
+    uint4 rid[64];       // Philox stream (s0, s1, s2) and first block of each row's normals
 };
 
 enum : int { kModePlain = 0, kModeStExact = 1, kModeStCvae = 2 };
@@ -597,7 +597,7 @@ __device__ __forceinline__ void stage_row(const PackedModel* pm, RenderLds& L, i
 #pragma unroll
     for (int k = 0; k < PI; ++k) row[lat + k] = (cond[k] - pm->mean_c[k]) * pm->inv_std_c[k];
     for (int q = lat + PI; q < kTile; ++q) row[q] = 0.0f;
-    L.rid[slot] = make_uint4(rng.id_lo, rng.id_hi, c0, 0u);
+    L.rid[slot] = make_uint4(rng.s0, rng.s1, rng.s2, c0);
     c0 += (uint32_t)((lat + PO + 3) >> 2);
 }
 
@@ -619,7 +619,7 @@ __device__ __forceinline__ int div_small(int q, int nb) {
 }
 
 // The normals of the n staged rows, drawn by the whole wave: row s needs
-// blocks rid[s].z .. rid[s].z + nb - 1 of its own Philox stream; the
+// blocks rid[s].w .. rid[s].w + nb - 1 of its own Philox stream; the
 // (row, block) tasks are spread over the 64 lanes.  Box-Muller pairs give
 // four normals per block: the first `latent` are the row's z, the next PO its
 // posterior noise -- the same values, in the same order, as if each lane drew
@@ -634,7 +634,7 @@ __device__ __forceinline__ void stage_normals(const RenderArgs& A, const PackedM
         const int slot = div_small(task, nb);
         const int j = task - slot * nb;
         const uint4 r = L.rid[slot];
-        const uint4 w = philox(r.z + (uint32_t)j, r.x, r.y, MS_TAG_RENDER_PATH, k0, k1);
+        const uint4 w = Rng{k0, k1, MS_TAG_RENDER_PATH, r.x, r.y, r.z}.block(r.w + (uint32_t)j);
         float nv[4];
         box_muller(u01(w.x), u01(w.y), nv[0], nv[1]);
         box_muller(u01(w.z), u01(w.w), nv[2], nv[3]);

@@ -45,8 +45,7 @@ constexpr int kOrderChunk = 4096;  // photons per block of the sort kernels
 
 // Parameters of training photon id (the walk kernel draws the same block).
 __device__ __forceinline__ void training_params(const WalkArgs& a, uint64_t id, float& st, float& g, float& phi) {
-    const uint4 pw = philox(0u, (uint32_t)id, (uint32_t)(id >> 32), MS_TAG_WALK_PARAM, (uint32_t)a.seed,
-                            (uint32_t)(a.seed >> 32));
+    const uint4 pw = make_rng(a.seed, MS_TAG_WALK_PARAM, id).block(0);
     const bool focus = u24(pw.w) <= a.focus_thr;
     st = (focus ? a.fst_lo : a.st_lo) * __builtin_amdgcn_exp2f(u01(pw.x) * (focus ? a.fst_log2_ratio : a.st_log2_ratio));
     g = __builtin_fmaf(focus ? a.fg_span : a.g_span, u01(pw.y), focus ? a.fg_lo : a.g_lo);
