@@ -133,7 +133,10 @@ __device__ __forceinline__ V3 v3(float x, float y, float z) { return V3{x, y, z}
 __device__ __forceinline__ V3 operator+(V3 a, V3 b) { return v3(a.x + b.x, a.y + b.y, a.z + b.z); }
 __device__ __forceinline__ V3 operator-(V3 a, V3 b) { return v3(a.x - b.x, a.y - b.y, a.z - b.z); }
 __device__ __forceinline__ V3 operator*(float s, V3 a) { return v3(s * a.x, s * a.y, s * a.z); }
-__device__ __forceinline__ float dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+// Fused in one order, so that every loop that evaluates it rounds alike.
+__device__ __forceinline__ float dot(V3 a, V3 b) {
+    return __builtin_fmaf(a.z, b.z, __builtin_fmaf(a.x, b.x, a.y * b.y));
+}
 __device__ __forceinline__ V3 fma3(float s, V3 a, V3 b) {
     return v3(__builtin_fmaf(s, a.x, b.x), __builtin_fmaf(s, a.y, b.y), __builtin_fmaf(s, a.z, b.z));
 }
@@ -152,13 +155,32 @@ __device__ __forceinline__ void onb(V3 n, V3& b1, V3& b2) {
     b2 = v3(b, sign + n.y * n.y * a, -n.y);
 }
 
+// Direction with polar cosine mu (sine s) and azimuth cosine ca, sine sa about
+// d: the rotation in the frame of onb(), with the order and the fused products
+// written out (and no others fused, also where one turn follows another), so
+// that every loop that turns a direction rounds alike.  The sign that onb()
+// takes from d.z is moved through the products, where it is exact, to sa and to
+// the result's z.
+__device__ __forceinline__ float times_sign(float v, float of) {
+    return __uint_as_float(__float_as_uint(v) ^ (__float_as_uint(of) & 0x80000000u));
+}
+__device__ __forceinline__ V3 turn(V3 d, float mu, float s, float ca, float sa) {
+#pragma clang fp contract(off)
+    const float az = __builtin_fabsf(d.z);
+    const float a = fast_rcp(1.0f + az);
+    const float b = (d.x * d.y) * -a;
+    const float b1x = __builtin_fmaf(-a, d.x * d.x, 1.0f), b2y = __builtin_fmaf(-(d.y * d.y), a, 1.0f);
+    const float ss = times_sign(sa, d.z);
+    const float tx = __builtin_fmaf(b, ss, b1x * ca), ty = __builtin_fmaf(b, ca, b2y * ss);
+    const float tz = __builtin_fmaf(-d.x, ca, -(d.y * ss));
+    const float nx = __builtin_fmaf(tx, s, d.x * mu), ny = __builtin_fmaf(ty, s, d.y * mu), nz = __builtin_fmaf(tz, s, az * mu);
+    const float il = fast_rsq(__builtin_fmaf(nz, nz, __builtin_fmaf(nx, nx, ny * ny)));
+    return v3(nx * il, ny * il, times_sign(nz * il, d.z));
+}
+
 // Direction with polar cosine mu (sine s) and azimuth (revolutions) about d.
 __device__ __forceinline__ V3 scatter(V3 d, float mu, float s, float az_rev) {
-    V3 b1, b2;
-    onb(d, b1, b2);
-    const float ca = cos_rev(az_rev), sa = sin_rev(az_rev);
-    V3 nd = mu * d + s * (ca * b1 + sa * b2);
-    return normalize(nd);
+    return turn(d, mu, s, cos_rev(az_rev), sin_rev(az_rev));
 }
 
 // Distance from x (inside) along unit d to the sphere |y|^2 = r2 about the
@@ -193,15 +215,20 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 
 // Per-wave ticket pool over a global 64-bit counter: lanes that need work
 // take consecutive tickets from the wave's private range and the wave
-// refills it with one atomic per `chunk` tickets.
+// refills it with one atomic per `chunk` tickets.  Wave w begins with tickets
+// w chunk .. w chunk + chunk - 1 and the counter past those of all waves; a
+// wave that has seen the end of the tickets asks no more: on one counter,
+// thousands of waves would wait for each other's atomics at either end.
 struct TicketPool {
     uint64_t next, end;
-    __device__ __forceinline__ void reset() {
-        next = 0;
-        end = 0;
+    bool dry;
+    __device__ __forceinline__ void reset(uint64_t wave, uint32_t chunk) {
+        next = wave * chunk;
+        end = next + chunk;
+        dry = false;
     }
-    // Returns this lane's ticket (meaningful where `need`).
-    __device__ __forceinline__ uint64_t take(bool need, unsigned long long* counter, uint32_t chunk) {
+    // Returns this lane's ticket (meaningful where `need`): work for it below n.
+    __device__ __forceinline__ uint64_t take(bool need, unsigned long long* counter, uint32_t chunk, uint64_t n) {
         const uint64_t mask = ballot(need);
         if (mask == 0) return 0;
         const uint32_t n_need = (uint32_t)__popcll(mask);
@@ -212,10 +239,13 @@ struct TicketPool {
             mine = next + rank;
             next += n_need;
         } else {
-            const int leader = __ffsll((long long)mask) - 1;
-            unsigned long long base = 0;
-            if (lane_id() == leader) base = atomicAdd(counter, (unsigned long long)chunk);
-            base = __shfl(base, leader);
+            unsigned long long base = n;
+            if (!dry) {
+                const int leader = __ffsll((long long)mask) - 1;
+                if (lane_id() == leader) base = atomicAdd(counter, (unsigned long long)chunk);
+                base = uniform_u64(__shfl(base, leader));
+                dry = base + chunk >= n;
+            }
             mine = rank < avail ? next + rank : base + (rank - avail);
             next = base + (n_need - avail);
             end = base + chunk;
@@ -238,6 +268,41 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
     }
     return v;
 }
+
+// A launch's totals: the waves of a block add theirs up in LDS, and the last
+// one to finish adds the block's to the global counters.  One atomic per wave
+// and counter, all on one cache line, took 60 us of a launch of 1500 waves.
+struct BlockTotals {
+    unsigned long long sum[4];
+    uint32_t finished;
+    // Every thread of the block, before the first add.
+    __device__ __forceinline__ void reset() {
+        if (threadIdx.x < 4) sum[threadIdx.x] = 0ull;
+        if (threadIdx.x == 0) finished = 0u;
+        __syncthreads();
+    }
+    // Once per wave, with its totals (the same in every lane): v[0..2] are
+    // added to the counters, v[3] is added or, with kMax, their maximum taken.
+    template <bool kMax>
+    __device__ __forceinline__ void add(const uint64_t* v, unsigned long long* counters) {
+        if (lane_id() != 0) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (kMax && q == 3) atomicMax(&sum[q], (unsigned long long)v[q]);
+            else if (v[q]) atomicAdd(&sum[q], (unsigned long long)v[q]);
+        }
+        __threadfence_block();
+        if (atomicAdd(&finished, 1u) != blockDim.x / 64 - 1) return;
+        __threadfence_block();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned long long t = sum[q];
+            if (t == 0) continue;
+            if (kMax && q == 3) atomicMax(counters + q, t);
+            else atomicAdd(counters + q, t);
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------
 // bfloat16 (round to nearest even) and FP8 E4M3 (OCP) conversions.

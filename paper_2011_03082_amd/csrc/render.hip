@@ -24,6 +24,7 @@
 namespace msst {
 
 constexpr int kRenderWaves = 4;
+constexpr uint32_t kTickets = 64;  // work units a wave takes at a time
 
 // Lane states: no path in flight (NEED: start a sample, take a work unit,
 // or wait for the parked path), tracing (FLY), waiting for a learned step
@@ -715,13 +716,13 @@ __device__ __forceinline__ int wave_prefix_small(int cnt, int& total) {
 // samples of its work unit one after the other and banks them in order.
 template <int MODE, int NP, bool GRID>
 __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, const float* lds_prims,
-                                            uint32_t (*tot)[64 * kRenderWaves]) {
+                                            uint32_t (*tot)[64 * kRenderWaves], BlockTotals& totals) {
     typename GeoSel<NP, GRID>::type G;
     constexpr bool kWaveLight = GeoSel<NP, GRID>::type::kWaveLight;
     G.init(A, lds_prims);
 
     TicketPool pool;
-    pool.reset();
+    pool.reset((uint64_t)blockIdx.x * kRenderWaves + (threadIdx.x >> 6), kTickets);
     int state = S_NEED;
     // current path
     Rng rng = make_rng(A.seed, MS_TAG_RENDER_PATH, 0);
@@ -806,7 +807,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             state = S_NEED;
         }
         const bool need = state == S_NEED && tot[U_UNIT][tid] == U_NONE;
-        const uint64_t tk = pool.take(need, A.ticket, 64);
+        const uint64_t tk = pool.take(need, A.ticket, kTickets, (uint64_t)A.n_units);
         if (need) {
             if (tk < (uint64_t)A.n_units) {
                 tot[U_UNIT][tid] = (uint32_t)tk;
@@ -1169,13 +1170,9 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         } while (!restart_due);
     }
     if (A.counters) {
-        const uint64_t a1 = wave_sum_u64(tot[T_EVENTS][tid]), a2 = wave_sum_u64(tot[T_STEPS][tid]),
-                       a3 = wave_sum_u64(tot[T_TRUNC][tid]);
-        if (lane_id() == 0) {
-            if (a1) atomicAdd(A.counters + 1, (unsigned long long)a1);
-            if (a2) atomicAdd(A.counters + 2, (unsigned long long)a2);
-            if (a3) atomicAdd(A.counters + 3, (unsigned long long)a3);
-        }
+        const uint64_t v[4] = {0, wave_sum_u64(tot[T_EVENTS][tid]), wave_sum_u64(tot[T_STEPS][tid]),
+                               wave_sum_u64(tot[T_TRUNC][tid])};
+        totals.add<false>(v, A.counters);
     }
 }
 
@@ -1192,6 +1189,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     __shared__ float lds_none[8];
     float* lds_prims = NP == 0 ? lds_dyn : lds_none;
     RenderLds& L = lds_all[threadIdx.x >> 6];
+    __shared__ BlockTotals totals;
+    // models that the check before this launch refused: nothing is traced
+    if (MODE == kModeStCvae && A.ticket[1] != 0) return;
+    totals.reset();
     if (NP == 0) {
         for (int q = threadIdx.x; q < A.n_prims * 8; q += blockDim.x) lds_prims[q] = A.prims[q];
         __syncthreads();
@@ -1208,11 +1209,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         const float t_max = A.sigma_t * __builtin_fminf(G.max_radius(), A.st_max * A.inv_sigma_t);
         const bool pays = !(A.min_chain > 0.0f) || 0.5f * t_max * t_max * (1.0f - A.g) >= A.min_chain;
         if (!(t_max >= A.tau_min) || !pays) {
-            render_loop<kModePlain, NP, GRID>(A, L, lds_prims, lds_tot);
+            render_loop<kModePlain, NP, GRID>(A, L, lds_prims, lds_tot, totals);
             return;
         }
     }
-    render_loop<MODE, NP, GRID>(A, L, lds_prims, lds_tot);
+    render_loop<MODE, NP, GRID>(A, L, lds_prims, lds_tot, totals);
 }
 
 // Per-pixel fixed-order reduction of the unit partials, added to the image
@@ -1268,7 +1269,9 @@ __global__ void render_reduce_kernel(int64_t npix, int n_chunks, int spp, const 
     }
 }
 
-__global__ void render_check_models(const RenderArgs A, unsigned long long* flag) {
+// ticket[0]: the counter past the tickets that the waves begin with;
+// ticket[1]: whether the models are refused.
+__global__ void render_check_models(const RenderArgs A, uint64_t first) {
     if (threadIdx.x != 0) return;
     const int want_in[3] = {2, 3, 7}, want_out[3] = {1, 3, 6};
     int ok = 1;
@@ -1279,20 +1282,15 @@ __global__ void render_check_models(const RenderArgs A, unsigned long long* flag
               (pm->precision == MS_PREC_BF16 || pm->precision == MS_PREC_FP8) && pm->n_linear >= 2 &&
               pm->n_linear <= kMaxLayers && pm->blocks == 1 && pm->width <= 16;
     }
-    *flag = ok ? 0ull : 1ull;
+    A.ticket[0] = first;
+    A.ticket[1] = ok ? 0ull : 1ull;
 }
 
-__global__ void render_zero_kernel(unsigned long long* ticket, unsigned long long* flag) {
+__global__ void render_start_kernel(unsigned long long* ticket, uint64_t first) {
     if (threadIdx.x == 0) {
-        ticket[0] = 0ull;
-        flag[0] = 0ull;
+        ticket[0] = first;
+        ticket[1] = 0ull;
     }
-}
-
-// With invalid models the ticket counter starts past the last unit, so the
-// render kernel does no work, and the reduction poisons the image.
-__global__ void render_gate_kernel(const unsigned long long* flag, unsigned long long* ticket, int64_t n_units) {
-    if (threadIdx.x == 0) ticket[0] = flag[0] ? (unsigned long long)n_units : 0ull;
 }
 
 // Conservative FP16 distance grid (the voxel-grid distance pre-process of
@@ -1495,17 +1493,14 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     A.counters = reinterpret_cast<unsigned long long*>(out->counters);
 
     hipStream_t hs = (hipStream_t)stream;
-    if (learned) {
-        hipLaunchKernelGGL(render_check_models, dim3(1), dim3(64), 0, hs, A, flag);
-        hipLaunchKernelGGL(render_gate_kernel, dim3(1), dim3(64), 0, hs, flag, A.ticket, A.n_units);
-    } else {
-        hipLaunchKernelGGL(render_zero_kernel, dim3(1), dim3(64), 0, hs, A.ticket, flag);
-    }
-    MS_LAUNCHED();
     const int bpc = desc->blocks_per_cu ? desc->blocks_per_cu : 4;
     int64_t blocks = (int64_t)cus * bpc;
     const int64_t need_blocks = (A.n_units + 255) / 256;
     if (blocks > need_blocks) blocks = need_blocks;
+    const uint64_t first = (uint64_t)blocks * kRenderWaves * kTickets;
+    if (learned) hipLaunchKernelGGL(render_check_models, dim3(1), dim3(64), 0, hs, A, first);
+    else hipLaunchKernelGGL(render_start_kernel, dim3(1), dim3(64), 0, hs, A.ticket, first);
+    MS_LAUNCHED();
     const int mode = desc->method == MS_METHOD_PLAIN_NEE ? kModePlain
                      : (desc->sampler == MS_SAMPLER_EXACT_WALK ? kModeStExact : kModeStCvae);
     const dim3 grid((unsigned)blocks), block(64 * kRenderWaves);

@@ -5,13 +5,13 @@
 // One photon per lane at a time.  Scattering-chain lengths are heavy tailed
 // (1 to ~10^5 events), so lanes take new photons from a per-wave ticket pool
 // as soon as theirs leaves the sphere: waves stay full until the global
-// ticket counter runs past n_photons, and every wave then exits.  With a few
-// photons per lane the end of the run is the last long chains on nearly empty
-// waves, so training walks are handed out longest expected chain first (a
-// counting sort of the photon ids by a bucket of sigma_t r and g); each
-// photon's result depends only on its id, so the order changes no output.
-#include "device.hpp"
+// ticket counter runs past n_photons.  The rest of the run is the last long
+// chains on nearly empty waves: training walks are handed out longest expected
+// chain first (a counting sort of the photon ids by a bucket of sigma_t r and
+// g), and a wave with few chains left walks them together.  Each photon's
+// result depends only on its id, so neither changes an output.
 #include "host.hpp"
+#include "mfma.hpp"
 
 namespace msst {
 
@@ -37,6 +37,7 @@ struct WalkArgs {
     unsigned long long* counters;
     unsigned long long* ticket;
     const uint32_t* order;  // ticket -> photon index (TRAINING), or null
+    int width;              // lanes of a wave that take photons; below 64, once
 };
 
 // Order buckets: more expected events first.
@@ -76,20 +77,23 @@ __global__ __launch_bounds__(256) void walk_order_count(const WalkArgs a, uint32
         if (h[b]) atomicAdd(&counts[b], h[b]);
 }
 
-// Exclusive prefix of the bucket counts (one wave, bucket order).
-__global__ void walk_order_scan(const uint32_t* counts, uint32_t* cursor) {
-    if (threadIdx.x != 0) return;
-    uint32_t acc = 0;
-    for (int b = 0; b < kOrderBuckets; ++b) {
-        cursor[b] = acc;
-        acc += counts[b];
-    }
-}
-
-__global__ __launch_bounds__(256) void walk_order_scatter(const WalkArgs a, uint32_t* cursor, uint32_t* order) {
-    __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets];
+__global__ __launch_bounds__(256) void walk_order_scatter(const WalkArgs a, const uint32_t* counts, uint32_t* cursor,
+                                                          uint32_t* order) {
+    __shared__ uint32_t h[kOrderBuckets], base[kOrderBuckets], first[kOrderBuckets];
     __shared__ uint8_t key[kOrderChunk];
     for (int b = threadIdx.x; b < kOrderBuckets; b += blockDim.x) h[b] = 0u;
+    if (threadIdx.x < 64) {
+        // where each bucket starts: every block adds the counts up for itself
+        const uint32_t c0 = counts[2 * threadIdx.x], c1 = counts[2 * threadIdx.x + 1];
+        uint32_t incl = c0 + c1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(incl, off);
+            if ((int)threadIdx.x >= off) incl += v;
+        }
+        first[2 * threadIdx.x] = incl - c0 - c1;
+        first[2 * threadIdx.x + 1] = incl - c1;
+    }
     __syncthreads();
     const uint64_t lo = (uint64_t)blockIdx.x * kOrderChunk;
     for (uint64_t i = lo + threadIdx.x; i < a.n && i < lo + kOrderChunk; i += blockDim.x) {
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(256) void walk_order_scatter(const WalkArgs a, uint
     }
     __syncthreads();
     for (int b = threadIdx.x; b < kOrderBuckets; b += blockDim.x) {
-        base[b] = h[b] ? atomicAdd(&cursor[b], h[b]) : 0u;
+        base[b] = h[b] ? first[b] + atomicAdd(&cursor[b], h[b]) : 0u;
         h[b] = 0u;
     }
     __syncthreads();
@@ -123,12 +127,29 @@ __device__ __forceinline__ void put3(float* base, uint64_t n, uint64_t i, V3 v) 
 // that the code is not issued every iteration for a few lanes.
 constexpr int kWalkRestartMin = 16;
 
+// Chains a wave has left, with no photons to take, when it starts to walk
+// them together.
+constexpr int kWalkTogether = 16;
+
+// What the events of the chains walked together draw: G consecutive events
+// for each of 64 / G chains, four padding entries after each chain's.
+struct alignas(16) WalkLds {
+    float4 turn[128];   // mu, sin theta, cosine and sine of the azimuth
+    float flight[128];  // flight length (inf: absorbed)
+    float pick[128];    // uniform of the event choice
+    float safe[32];     // per four events: |x|^2 below which none of them can leave the sphere
+    uint32_t lane[64];  // lane that holds the k-th live chain
+};
+
 template <int MODE>
 __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
+    __shared__ WalkLds lds_all[4];
+    __shared__ BlockTotals totals;
+    totals.reset();
     TicketPool pool;
-    pool.reset();
+    pool.reset((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6), a.width);
     // lane state: walking, ended (record not yet written), idle, done
-    bool active = false, ended = false, done = false;
+    bool active = false, ended = false, done = lane_id() >= a.width;
     bool absorbed = false, truncated = false;
     uint64_t i = 0;
     Rng rng = make_rng(a.seed, MS_TAG_WALK_EVENT, 0);
@@ -139,47 +160,219 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
     const float r2 = MODE == MS_WALK_ANALOG ? a.r2 : 1.0f;
     uint64_t n_events = 0, n_abs = 0, n_trunc = 0, n_max = 0;
 
+    // The record of a finished photon; x, d: where it ended and its direction.
+    auto finish = [&](uint32_t nev, bool absorbed, bool truncated, V3 x, V3 d) __attribute__((always_inline)) {
+        n_events += nev;
+        n_abs += absorbed;
+        n_trunc += truncated;
+        n_max = nev > n_max ? nev : n_max;
+        const uint64_t n = a.n;
+        if (a.params) {
+            put3(a.params, n, i, v3(MODE == MS_WALK_ANALOG ? a.st_report : st, g, phi));
+        }
+        if (a.n_scatter) a.n_scatter[i] = nev;
+        if (a.absorbed) a.absorbed[i] = (uint8_t)absorbed;
+        if (a.truncated) a.truncated[i] = (uint8_t)truncated;
+        put3(a.exit_pos, n, i, x);
+        put3(a.exit_dir, n, i, d);
+        // exit frame of Sec. 4.1 after rotating by -psi about w_in = z
+        const float ir = 1.0f / r;
+        const V3 xh = ir * x;
+        const float sin_t = __builtin_sqrtf(__builtin_fmaf(xh.x, xh.x, xh.y * xh.y));
+        float cp = 1.0f, sp = 0.0f;
+        if (sin_t > 0.0f) {
+            cp = xh.x / sin_t;
+            sp = xh.y / sin_t;
+        }
+        // fused products written out: this code is inlined twice
+        auto turned = [&](V3 v) __attribute__((always_inline)) {
+            return v3(__builtin_fmaf(v.y, sp, v.x * cp), __builtin_fmaf(v.y, cp, -(v.x * sp)), v.z);
+        };
+        if (a.exit_param) {
+            const V3 wp = turned(d);
+            put3(a.exit_param, n, i, v3(xh.z, wp.y, __builtin_fmaf(wp.x, xh.z, -(wp.z * sin_t))));
+        }
+        if (MODE == MS_WALK_TRAINING) {
+            if (a.event_index) a.event_index[i] = k;
+            put3(a.event_pos, n, i, turned(ir * xk));
+            put3(a.event_dir, n, i, turned(wk));
+        }
+    };
+
+    // The last chains of a wave, walked together.  A launch ends with a few
+    // long chains (2 x 10^5 events of one photon in 2^22), each an event after
+    // the other on a lane of its own: bound by the instructions of one event,
+    // whatever lanes are idle.  Two thirds of those do not depend on where the
+    // photon is: here a chain has G = 64 / (chains left) lanes, each draws
+    // one of its next G events, and then all of them walk the G events on the
+    // same state, reading the draws from LDS.  One wave issues an instruction
+    // every 6 cycles: an event took 0.43 us alone and takes 0.11 (about 38
+    // instructions, nearly all of them the turn of the direction); 2^22
+    // training walks 105 -> 56 ms, 2^16 73 -> 14 ms.
+    auto walk_together = [&]() __attribute__((always_inline)) {
+        WalkLds& L = lds_all[threadIdx.x >> 6];
+        const int lane = lane_id();
+        bool leader = true;  // of the lanes that hold one chain, the one that writes its record
+        for (uint64_t live = ballot(active); live != 0; live = ballot(active && leader)) {
+            const int n_live = __popcll(live);
+            const int lg = n_live > 1 ? 6 - (32 - __builtin_clz((uint32_t)(n_live - 1))) : 6;
+            const int G = 1 << lg, chain = lane >> lg, slot0 = chain * (G + 4);
+            if (active && leader) L.lane[rank_in(live)] = (uint32_t)lane;
+            wave_sync();
+            const int src = (int)L.lane[chain < n_live ? chain : 0];
+            wave_sync();
+            auto from = [src](uint32_t v) __attribute__((always_inline)) { return (uint32_t)__shfl((int)v, src); };
+            auto fromf = [src](float v) __attribute__((always_inline)) { return __shfl(v, src); };
+            i = (uint64_t)from((uint32_t)i) | (uint64_t)from((uint32_t)(i >> 32)) << 32;
+            rng.s0 = from(rng.s0);
+            rng.s1 = from(rng.s1);
+            rng.s2 = from(rng.s2);
+            c0 = from(c0);
+            nev = from(nev);
+            k = from(k);
+            x = v3(fromf(x.x), fromf(x.y), fromf(x.z));
+            d = v3(fromf(d.x), fromf(d.y), fromf(d.z));
+            xk = v3(fromf(xk.x), fromf(xk.y), fromf(xk.z));
+            wk = v3(fromf(wk.x), fromf(wk.y), fromf(wk.z));
+            st = fromf(st);
+            inv_st = fromf(inv_st);
+            g = fromf(g);
+            phi = fromf(phi);
+            inv_phi = fromf(inv_phi);
+            resv = fromf(resv);
+            active = chain < n_live;
+            leader = (lane & (G - 1)) == 0;
+            // the draw that stands for "kept" under uniform weighting is 0
+            // (else inf), against a reservoir that stays 1
+            const bool uniform = a.weighting == MS_EVENT_UNIFORM;
+            const float grow = uniform ? 0.0f : inv_phi;
+            if (uniform) resv = 0.0f;
+            // steps until the first chain reaches max_events, at most G at once
+            uint32_t left = active ? a.max_events - nev : 0xFFFFFFFFu;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)left, off);
+                left = o < left ? o : left;
+            }
+            left = uniform_u32(left);
+            int n_now = n_live;
+            do {
+                const uint32_t steps = left < (uint32_t)G ? left : (uint32_t)G;
+                const uint32_t mine = (uint32_t)(lane & (G - 1));
+                const uint4 w = rng.block(c0 + mine);
+                const HgSample h = hg_sample(g, u01(w.y));
+                const float az = u01(w.z);
+                float l = -flight_ln(u01(w.x)) * inv_st, u = 0.0f;
+                if (MODE == MS_WALK_ANALOG) {
+                    if (active && u24(w.w) > a.surv_thr) l = INFINITY;
+                } else if (uniform) {
+                    u = (uint64_t)u24(w.w) * (nev + mine + 1u) <= (1ull << 24) ? 0.0f : INFINITY;
+                } else {
+                    u = u01(w.w);
+                }
+                L.turn[slot0 + mine] = make_float4(h.mu, h.sin_t, cos_rev(az), sin_rev(az));
+                L.flight[slot0 + mine] = l;
+                L.pick[slot0 + mine] = u;
+                // the flights of four events end to end, rounded up
+                float l4 = l + __shfl_xor(l, 1);
+                l4 += __shfl_xor(l4, 2);
+                const float room = 0.9999f * r - l4;
+                if ((lane & 3) == 0) L.safe[lane >> 2] = !active ? INFINITY : room > 0.0f ? room * room : 0.0f;
+                wave_sync();
+                // The reservoir only grows (to a rounding): none of these
+                // events is chosen if none would be against its present value,
+                // and past 2^24 no uniform of any later one is small enough.
+                const bool choose = MODE == MS_WALK_TRAINING && ballot(active && u * resv <= 1.0001f) != 0;
+                const bool grown = MODE == MS_WALK_ANALOG || ballot(active && !(resv > 0x1p25f)) == 0;
+                // where a chain that leaves in these steps ends
+                bool left_now = false, gone = false;
+                uint32_t n_end = 0;
+                V3 xe = x, de = d;
+                auto step = [&](uint32_t e) __attribute__((always_inline)) {
+                    const float4 t = L.turn[slot0 + e];
+                    const float l = L.flight[slot0 + e];
+                    if (MODE == MS_WALK_TRAINING) {
+                        resv = __builtin_fmaf(resv, grow, 1.0f);
+                        if (active && L.pick[slot0 + e] * resv <= 1.0f) {
+                            xk = x;
+                            wk = d;
+                            k = nev + e + 1u;
+                        }
+                    }
+                    const V3 dn = turn(d, t.x, t.y, t.z, t.w);
+                    const V3 xn = fma3(l, dn, x);
+                    if (active && !(dot(xn, xn) < r2)) {
+                        active = false;
+                        left_now = true;
+                        n_end = nev + e + 1u;
+                        gone = MODE == MS_WALK_ANALOG && l == INFINITY;
+                        xe = gone ? x : fma3(sphere_exit(x, dn, r2), dn, x);
+                        de = gone ? d : dn;
+                    }
+                    x = xn;
+                    d = dn;
+                };
+                // Four events at a time without looking; where one of them is
+                // chosen, or may leave the sphere and does, one by one.
+                uint32_t e = 0;
+                const float4* tp = L.turn + slot0;
+                const float4* lp = reinterpret_cast<const float4*>(L.flight + slot0);
+                const float* sp = L.safe + (chain << lg >> 2);
+                for (; e + 4u <= steps; e += 4u) {
+                    const float4 t0 = tp[0], t1 = tp[1], t2 = tp[2], t3 = tp[3], lq = *lp;
+                    const float safe = *sp;
+                    tp += 4;
+                    ++lp;
+                    ++sp;
+                    const V3 d0 = turn(d, t0.x, t0.y, t0.z, t0.w), x0 = fma3(lq.x, d0, x);
+                    const V3 d1 = turn(d0, t1.x, t1.y, t1.z, t1.w), x1 = fma3(lq.y, d1, x0);
+                    const V3 d2 = turn(d1, t2.x, t2.y, t2.z, t2.w), x2 = fma3(lq.z, d2, x1);
+                    const V3 d3 = turn(d2, t3.x, t3.y, t3.z, t3.w), x3 = fma3(lq.w, d3, x2);
+                    bool look = ballot(!(dot(x, x) < safe)) != 0;
+                    if (look)
+                        look = ballot(active && !(dot(x0, x0) < r2 && dot(x1, x1) < r2 && dot(x2, x2) < r2 && dot(x3, x3) < r2)) != 0;
+                    if (look || choose) {
+#pragma unroll 1
+                        for (uint32_t q = 0; q < 4; ++q) step(e + q);
+                    } else {
+                        x = x3;
+                        d = d3;
+                        if (!grown) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) resv = __builtin_fmaf(resv, grow, 1.0f);
+                        }
+                    }
+                }
+#pragma unroll 1
+                for (; e < steps; ++e) step(e);
+                nev += steps;
+                c0 += steps;
+                left -= steps;
+                bool cut = false;
+                if (left == 0 && active && nev >= a.max_events) {
+                    active = false;
+                    left_now = cut = true;
+                    n_end = nev;
+                    xe = x;
+                    de = d;
+                }
+                if (left_now && leader) finish(n_end, gone, cut, xe, de);
+                n_now = __popcll(ballot(active && leader));
+                wave_sync();
+            } while (left != 0 && (2 * n_now > 64 / G || (G == 64 && n_now > 0)));
+        }
+    };
+
+    bool due = true;
     for (;;) {
-        const uint64_t rmask = ballot(!active && !done);
-        if (rmask != 0 && (__popcll(rmask) >= kWalkRestartMin || ballot(active) == 0)) {
+        if (due) {
             if (ended) {
-                // the record of the finished photon; x holds its exit point
+                // x holds the exit point
                 ended = false;
-                n_events += nev;
-                n_abs += absorbed;
-                n_trunc += truncated;
-                n_max = nev > n_max ? nev : n_max;
-                const uint64_t n = a.n;
-                if (a.params) {
-                    put3(a.params, n, i, v3(MODE == MS_WALK_ANALOG ? a.st_report : st, g, phi));
-                }
-                if (a.n_scatter) a.n_scatter[i] = nev;
-                if (a.absorbed) a.absorbed[i] = (uint8_t)absorbed;
-                if (a.truncated) a.truncated[i] = (uint8_t)truncated;
-                put3(a.exit_pos, n, i, x);
-                put3(a.exit_dir, n, i, d);
-                // exit frame of Sec. 4.1 after rotating by -psi about w_in = z
-                const float ir = 1.0f / r;
-                const V3 xh = ir * x;
-                const float sin_t = __builtin_sqrtf(xh.x * xh.x + xh.y * xh.y);
-                float cp = 1.0f, sp = 0.0f;
-                if (sin_t > 0.0f) {
-                    cp = xh.x / sin_t;
-                    sp = xh.y / sin_t;
-                }
-                if (a.exit_param) {
-                    const V3 wp = v3(cp * d.x + sp * d.y, -sp * d.x + cp * d.y, d.z);
-                    put3(a.exit_param, n, i, v3(xh.z, wp.y, wp.x * xh.z - wp.z * sin_t));
-                }
-                if (MODE == MS_WALK_TRAINING) {
-                    if (a.event_index) a.event_index[i] = k;
-                    const V3 xs = ir * xk;
-                    put3(a.event_pos, n, i, v3(cp * xs.x + sp * xs.y, -sp * xs.x + cp * xs.y, xs.z));
-                    put3(a.event_dir, n, i, v3(cp * wk.x + sp * wk.y, -sp * wk.x + cp * wk.y, wk.z));
-                }
+                finish(nev, absorbed, truncated, x, d);
             }
             const bool need = !active && !done;
-            const uint64_t t = pool.take(need, a.ticket, 64);
+            const uint64_t t = pool.take(need, a.ticket, a.width, a.n);
             if (need) {
                 if (t < a.n) {
                     i = a.order ? a.order[t] : t;
@@ -189,7 +382,8 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                     if (MODE == MS_WALK_TRAINING) {
                         training_params(a, id, st, g, phi);
                         inv_st = 1.0f / st;
-                        inv_phi = 1.0f / phi;
+                        // finite, so that the reservoir's first step gives 1
+                        inv_phi = __builtin_fminf(1.0f / phi, 0x1.fffffep127f);
                     }
                     x = v3(0, 0, 0);
                     d = v3(0, 0, 1);
@@ -203,73 +397,79 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                     done = true;
                 }
             }
-        }
-        if (ballot(!done) == 0) break;
-        if (!active) continue;
-
-        ++nev;
-        const uint4 w = rng.block(c0++);
-        bool stop = false;
-        absorbed = false;
-        truncated = false;
-        V3 xe = x;
-        if (MODE == MS_WALK_ANALOG) {
-            if (u24(w.w) > a.surv_thr) {
-                absorbed = true;
-                stop = true;
-            }
-        } else {
-            bool keep;
-            if (a.weighting == MS_EVENT_UNIFORM) {
-                keep = (uint64_t)u24(w.w) * nev <= (1ull << 24);
-            } else {
-                resv = nev == 1 ? 1.0f : __builtin_fmaf(resv, inv_phi, 1.0f);
-                keep = u01(w.w) * resv <= 1.0f;
-            }
-            if (keep) {
-                xk = x;
-                wk = d;
-                k = nev;
+            // with fewer than 64 lanes there is a wave for every `width`
+            // photons, and each takes its own once
+            if (a.width < 64) done = !active;
+            const uint64_t dmask = ballot(done);
+            if (dmask == ~0ull) break;
+            if (dmask != 0 && __popcll(ballot(active)) <= kWalkTogether) {
+                walk_together();
+                break;
             }
         }
-        if (!stop) {
-            const HgSample h = hg_sample(g, u01(w.y));
-            d = scatter(d, h.mu, h.sin_t, u01(w.z));
-            const float l = -flight_ln(u01(w.x)) * inv_st;
-            const V3 xn = fma3(l, d, x);
-            if (!(dot(xn, xn) < r2)) {
-                xe = fma3(sphere_exit(x, d, r2), d, x);
-                stop = true;
-            } else {
-                x = xn;
-                if (nev >= a.max_events) {
-                    truncated = true;
-                    xe = x;
+        if (active) {
+            ++nev;
+            const uint4 w = rng.block(c0++);
+            bool stop = false;
+            absorbed = false;
+            truncated = false;
+            V3 xe = x;
+            if (MODE == MS_WALK_ANALOG) {
+                if (u24(w.w) > a.surv_thr) {
+                    absorbed = true;
                     stop = true;
                 }
+            } else {
+                bool keep;
+                if (a.weighting == MS_EVENT_UNIFORM) {
+                    keep = (uint64_t)u24(w.w) * nev <= (1ull << 24);
+                } else {
+                    resv = __builtin_fmaf(resv, inv_phi, 1.0f);
+                    keep = u01(w.w) * resv <= 1.0f;
+                }
+                if (keep) {
+                    xk = x;
+                    wk = d;
+                    k = nev;
+                }
+            }
+            if (!stop) {
+                const HgSample h = hg_sample(g, u01(w.y));
+                d = scatter(d, h.mu, h.sin_t, u01(w.z));
+                const float l = -flight_ln(u01(w.x)) * inv_st;
+                const V3 xn = fma3(l, d, x);
+                if (!(dot(xn, xn) < r2)) {
+                    xe = fma3(sphere_exit(x, d, r2), d, x);
+                    stop = true;
+                } else {
+                    x = xn;
+                    if (nev >= a.max_events) {
+                        truncated = true;
+                        xe = x;
+                        stop = true;
+                    }
+                }
+            }
+            if (stop) {
+                active = false;
+                ended = true;
+                x = xe;
             }
         }
-        if (stop) {
-            active = false;
-            ended = true;
-            x = xe;
-        }
+        const uint64_t rmask = ballot(!active && !done);
+        due = rmask != 0 && (__popcll(rmask) >= kWalkRestartMin || ballot(active) == 0);
     }
     if (a.counters) {
-        const uint64_t se = wave_sum_u64(n_events), sa = wave_sum_u64(n_abs), stc = wave_sum_u64(n_trunc);
-        const uint64_t mx = wave_max_u64(n_max);
-        if (lane_id() == 0) {
-            atomicAdd(a.counters + 0, (unsigned long long)se);
-            atomicAdd(a.counters + 1, (unsigned long long)sa);
-            atomicAdd(a.counters + 2, (unsigned long long)stc);
-            atomicMax(a.counters + 3, (unsigned long long)mx);
-        }
+        const uint64_t v[4] = {wave_sum_u64(n_events), wave_sum_u64(n_abs), wave_sum_u64(n_trunc), wave_max_u64(n_max)};
+        totals.add<true>(v, a.counters);
     }
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p, int n) {
+// The ticket counter past the tickets that the waves begin with, and zeros
+// after it.
+__global__ void walk_ticket_kernel(unsigned long long* p, int n, uint64_t first) {
     const int t = threadIdx.x;
-    if (t < n) p[t] = 0ull;
+    if (t < n) p[t] = t == 0 ? first : 0ull;
 }
 
 }  // namespace msst
@@ -279,7 +479,7 @@ extern "C" {
 ms_status ms_random_walk_workspace_size(const ms_walk_desc* desc, size_t* bytes) {
     MS_REQUIRE(desc != nullptr && bytes != nullptr, "ms_random_walk_workspace_size: NULL argument");
     // ticket counter; for training walks of fewer than 2^32 photons also the
-    // order buckets and the photon order (4 bytes per photon)
+    // order buckets, their cursors and the photon order (4 bytes per photon)
     *bytes = 256;
     if (desc->mode == MS_WALK_TRAINING && desc->n_photons < (1ull << 32))
         *bytes = 2048 + msst::align_up((size_t)desc->n_photons * 4, 256);
@@ -367,6 +567,28 @@ ms_status ms_random_walk(const ms_walk_desc* desc, const ms_walk_out* out, void*
     a.counters = reinterpret_cast<unsigned long long*>(out->counters);
     a.ticket = reinterpret_cast<unsigned long long*>(workspace_dev);
 
+    // Three blocks (as many as fit) keep VALU issue busy: 2^24 training walks
+    // in 120 / 104 / 104 ms with two / three / four, 2^22 in 59 / 56 / 59 ms; the
+    // end of a launch no longer depends on how many waves share a SIMD.
+    const int bpc = d.blocks_per_cu ? d.blocks_per_cu : 3;
+    // A few photons with long chains are spread over all waves: the fewer
+    // chains a wave has, the sooner they walk together (2^16 training walks
+    // 29 -> 14 ms, 4096 22 -> 10 ms).  Where even the longest chains are short
+    // (the expected events of the thickest, most backward medium, as in
+    // order_bucket, or the event and absorption limits) full waves finish
+    // them sooner: 10^5 analog walks of 17 events 0.14 ms, spread 0.25 ms.
+    const bool training = d.mode == MS_WALK_TRAINING;
+    const bool focus = training && d.focus_fraction > 0.0;
+    const double tau = training ? fmax(d.st_range[1], focus ? d.focus_st_range[1] : 0.0) : d.sigma_t * d.radius;
+    const double g_lo = training ? fmin(d.g_range[0], focus ? d.focus_g_range[0] : 1.0) : d.g;
+    double longest = fmin(1.0 + tau + 0.35 * tau * tau * (1.0 - g_lo), (double)a.max_events);
+    if (!training && d.albedo < 1.0) longest = fmin(longest, 1.0 / (1.0 - d.albedo));
+    a.width = 8;
+    while (a.width < 64 && d.n_photons > (uint64_t)a.width * 4 * cus * bpc) a.width *= 2;
+    if (longest < 256.0) a.width = d.n_photons <= (uint64_t)16 * 4 * cus ? 16 : 64;
+    uint64_t blocks = (d.n_photons + 4 * a.width - 1) / (4 * a.width);
+    if (blocks > (uint64_t)cus * bpc) blocks = (uint64_t)cus * bpc;
+    const uint64_t first = blocks * 4 * a.width;
     hipStream_t s = (hipStream_t)stream;
     if (ws_need > 256) {
         // longest expected chains first: counts, prefix, scatter of the ids
@@ -374,19 +596,14 @@ ms_status ms_random_walk(const ms_walk_desc* desc, const ms_walk_out* out, void*
         uint32_t* cursor = counts + kOrderBuckets;
         uint32_t* order = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(workspace_dev) + 2048);
         const unsigned ob = (unsigned)((d.n_photons + kOrderChunk - 1) / kOrderChunk);
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<unsigned long long*>(counts),
-                           kOrderBuckets / 2);
+        hipLaunchKernelGGL(walk_ticket_kernel, dim3(1), dim3(256), 0, s, a.ticket, 128 + kOrderBuckets, first);
         hipLaunchKernelGGL(walk_order_count, dim3(ob), dim3(256), 0, s, a, counts);
-        hipLaunchKernelGGL(walk_order_scan, dim3(1), dim3(64), 0, s, counts, cursor);
-        hipLaunchKernelGGL(walk_order_scatter, dim3(ob), dim3(256), 0, s, a, cursor, order);
+        hipLaunchKernelGGL(walk_order_scatter, dim3(ob), dim3(256), 0, s, a, (const uint32_t*)counts, cursor, order);
         a.order = order;
+    } else {
+        hipLaunchKernelGGL(walk_ticket_kernel, dim3(1), dim3(64), 0, s, a.ticket, 1, first);
     }
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, a.ticket, 1);
     MS_LAUNCHED();
-    const int bpc = d.blocks_per_cu ? d.blocks_per_cu : 2;
-    uint64_t blocks = (uint64_t)cus * bpc;
-    const uint64_t need = (d.n_photons + 255) / 256;
-    if (blocks > need) blocks = need;
     if (d.mode == MS_WALK_ANALOG)
         hipLaunchKernelGGL(walk_kernel<MS_WALK_ANALOG>, dim3((unsigned)blocks), dim3(256), 0, s, a);
     else

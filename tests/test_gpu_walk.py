@@ -170,3 +170,30 @@ def test_focus_weighted_parameters_and_paths(msst, oracle):
     assert inside.mean() > 0.4
     same = (g["n_scatter"].astype(np.int64) == o["n_scatter"]) & (g["event_index"].astype(np.int64) == o["event_index"])
     assert 1 - same[st < 20].mean() < 1e-3
+
+
+@pytest.mark.parametrize("kw", [dict(mode=1), dict(mode=1, event_weighting=1), dict(mode=1, max_events=70),
+                                dict(mode=1, max_events=6, event_weighting=1),
+                                dict(mode=1, st_range=(150.0, 200.0), albedo_range=(1.0, 1.0)),
+                                dict(sigma_t=40.0, g=-0.5, albedo=1.0), dict(sigma_t=40.0, g=-0.5, albedo=0.999),
+                                dict(sigma_t=30.0, g=0.0, albedo=1.0, max_events=64), dict(albedo=0.0),
+                                dict(sigma_t=8.0, radius=2.5, albedo=0.98)])
+def test_chains_walked_together_are_the_same(msst, kw):
+    """A wave with few chains left walks them together (their draws made by
+    the idle lanes), full waves walk one chain per lane.  The same photons in
+    one launch of full waves and in launches of 1 to 1000 (4 to 64 lanes per
+    chain, blocks of events cut by max_events, absorption and exits anywhere in
+    a block) give the same records bit for bit."""
+    announce(f"walk together {kw}")
+    keys = ["n_scatter", "absorbed", "truncated", "exit_pos", "exit_dir", "exit_param", "params"]
+    keys += ["event_index", "event_pos", "event_dir"] if kw.get("mode") else []
+    full = to_np(msst.random_walk(33000, seed=21, blocks_per_cu=1, **kw))
+    at = 0
+    for n in (1, 3, 9, 64, 1000):
+        part = to_np(msst.random_walk(n, seed=21, photon_offset=at, **kw))
+        for k in keys:
+            np.testing.assert_array_equal(full[k][..., at:at + n], part[k], err_msg=f"{k} n={n}")
+        c = part["counters"]
+        assert c[0] == part["n_scatter"].astype(np.int64).sum() and c[3] == part["n_scatter"].max()
+        assert c[1] == part["absorbed"].sum() and c[2] == part["truncated"].sum()
+        at += n
