@@ -408,10 +408,11 @@ class Renderer:
         return {k: torch.stack([p[k] for p in planes]) for k in planes[0]}
 
 
-def column_moments(x):
+def column_moments(x, out=None):
     """FP64 column mean / std of a [n, dim] device float32 tensor as a [64] stats half."""
     n, dim = x.shape
-    out = torch.zeros(32, dtype=torch.float64, device=x.device)
+    if out is None:
+        out = torch.zeros(32, dtype=torch.float64, device=x.device)
     ws = torch.empty(ms_column_moments_workspace_size(n, dim), dtype=torch.uint8, device=x.device)
     ms_column_moments(x, n, dim, out, ws)
     return out
@@ -419,12 +420,8 @@ def column_moments(x):
 
 def make_stats(cond, target):
     """Standardisation constants [mean_c, std_c, mean_y, std_y] (16 each) on the device."""
-    mc, my = column_moments(cond), column_moments(target)
     st = torch.zeros(64, dtype=torch.float64, device=cond.device)
-    st[16:32] = 1.0
-    st[48:64] = 1.0
-    st[: cond.shape[1]] = mc[: cond.shape[1]]
-    st[16:16 + cond.shape[1]] = mc[16:16 + cond.shape[1]]
-    st[32:32 + target.shape[1]] = my[: target.shape[1]]
-    st[48:48 + target.shape[1]] = my[16:16 + target.shape[1]]
+    st.view(2, 2, 16)[:, 1] = 1.0
+    column_moments(cond, st[:32])
+    column_moments(target, st[32:])
     return st

@@ -95,51 +95,74 @@ __global__ void cvae_init_kernel(Shape s, uint64_t seed, float* master, int n_pa
 // ---------------------------------------------------------------------------
 // features (Sec. 4.2 model inputs; LengthGen target dequantised)
 
-__global__ void cvae_features_kernel(int model, int64_t n_out, const int64_t* rows, int64_t n, const float* params3,
-                                     const uint32_t* n_scatter, const float* exit_param, const float* event_pos,
-                                     const float* event_dir, uint64_t seed, uint64_t id_offset, const double* stats,
-                                     float* cond, float* target) {
-    for (int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; o < n_out;
-         o += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = rows ? rows[o] : o;
-        const float lst = logf(params3[i]), g = params3[n + i], phi = params3[2 * n + i];
-        const float N = (float)n_scatter[i];
-        float c[7], y[6];
-        int pc, py;
-        if (model == MS_MODEL_LENGTH) {
-            const Rng r = make_rng(seed, MS_TAG_DEQUANT, id_offset + (uint64_t)i);
-            const float u = u01(r.block(0).x);
+// (float)((c - mean) / std) in FP64 through the reciprocal and one correction
+// (three operations; FP64 division takes a dozen), the division itself where
+// the reciprocal or the quotient is not finite.
+__device__ __forceinline__ float standardised(float c, double mean, double std, double inv) {
+    const double d = (double)c - mean, q = d * inv;
+    const double r = __builtin_fma(__builtin_fma(-q, std, d), inv, q);
+    return (float)(__builtin_isfinite(r) ? r : d / std);
+}
+
+constexpr int kFeatThreads = 256;
+
+// Bound by HBM (EventGen: 60 bytes gathered and 52 written per row): a
+// block's rows go through LDS so that they are written in whole lines.  2^22
+// records, 2.6e6 EventGen rows 112 -> 66 us.
+template <int MODEL>
+__global__ __launch_bounds__(kFeatThreads) void cvae_features_kernel(int64_t n_out, const int64_t* rows, int64_t n,
+                                                                     const float* params3, const uint32_t* n_scatter,
+                                                                     const float* exit_param, const float* event_pos,
+                                                                     const float* event_dir, uint64_t seed,
+                                                                     uint64_t id_offset, const double* stats,
+                                                                     float* cond, float* target) {
+    constexpr int PC = MODEL == MS_MODEL_LENGTH ? 2 : MODEL == MS_MODEL_PATH ? 3 : 7;
+    constexpr int PY = MODEL == MS_MODEL_LENGTH ? 1 : MODEL == MS_MODEL_PATH ? 3 : 6;
+    __shared__ float cs[kFeatThreads * PC], ys[kFeatThreads * PY];
+    __shared__ double inv_std[PC + PY];
+    const int t = threadIdx.x;
+    if (stats && t < PC + PY) inv_std[t] = 1.0 / stats[t < PC ? 16 + t : 48 + t - PC];
+    __syncthreads();
+    for (int64_t o0 = blockIdx.x * (int64_t)kFeatThreads; o0 < n_out; o0 += (int64_t)gridDim.x * kFeatThreads) {
+        const int64_t o = o0 + t;
+        if (o < n_out) {
+            const int64_t i = rows ? rows[o] : o;
+            const float lst = logf(params3[i]), g = params3[n + i];
+            const float N = (float)n_scatter[i];
+            float c[PC], y[PY];
             c[0] = lst;
             c[1] = g;
-            y[0] = logf(N + u - 0.5f);
-            pc = 2;
-            py = 1;
-        } else if (model == MS_MODEL_PATH) {
-            c[0] = lst;
-            c[1] = g;
-            c[2] = logf(N);
-            for (int k = 0; k < 3; ++k) y[k] = exit_param[k * n + i];
-            pc = 3;
-            py = 3;
-        } else {
-            c[0] = lst;
-            c[1] = g;
-            c[2] = phi;
-            for (int k = 0; k < 3; ++k) c[3 + k] = exit_param[k * n + i];
-            c[6] = logf(N);
-            for (int k = 0; k < 3; ++k) {
-                y[k] = event_pos[k * n + i];
-                y[3 + k] = event_dir[k * n + i];
+            if (MODEL == MS_MODEL_LENGTH) {
+                const Rng r = make_rng(seed, MS_TAG_DEQUANT, id_offset + (uint64_t)i);
+                const float u = u01(r.block(0).x);
+                y[0] = logf(N + u - 0.5f);
+            } else if (MODEL == MS_MODEL_PATH) {
+                c[PC - 1] = logf(N);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) y[k % PY] = exit_param[k * n + i];
+            } else {
+                c[2 % PC] = params3[2 * n + i];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) c[(3 + k) % PC] = exit_param[k * n + i];
+                c[PC - 1] = logf(N);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    y[k % PY] = event_pos[k * n + i];
+                    y[(3 + k) % PY] = event_dir[k * n + i];
+                }
             }
-            pc = 7;
-            py = 6;
+#pragma unroll
+            for (int k = 0; k < PC; ++k)
+                cs[t * PC + k] = stats ? standardised(c[k], stats[k], stats[16 + k], inv_std[k]) : c[k];
+#pragma unroll
+            for (int k = 0; k < PY; ++k)
+                ys[t * PY + k] = stats ? standardised(y[k], stats[32 + k], stats[48 + k], inv_std[PC + k]) : y[k];
         }
-        if (stats) {
-            for (int k = 0; k < pc; ++k) c[k] = (float)((c[k] - stats[k]) / stats[16 + k]);
-            for (int k = 0; k < py; ++k) y[k] = (float)((y[k] - stats[32 + k]) / stats[48 + k]);
-        }
-        for (int k = 0; k < pc; ++k) cond[o * pc + k] = c[k];
-        for (int k = 0; k < py; ++k) target[o * py + k] = y[k];
+        __syncthreads();
+        const int m = n_out - o0 < kFeatThreads ? (int)(n_out - o0) : kFeatThreads;
+        for (int q = t; q < m * PC; q += kFeatThreads) cond[o0 * PC + q] = cs[q];
+        for (int q = t; q < m * PY; q += kFeatThreads) target[o0 * PY + q] = ys[q];
+        __syncthreads();
     }
 }
 
@@ -148,100 +171,201 @@ __global__ void cvae_features_kernel(int model, int64_t n_out, const int64_t* ro
 
 constexpr int kSelPerBlock = 2048;  // 256 threads x 8 consecutive rows
 
-__device__ __forceinline__ bool row_selected(int64_t i, int64_t n, const uint32_t* ns, const uint32_t* ek,
-                                             uint32_t min_n, uint32_t min_k) {
-    return i < n && ns[i] >= min_n && (ek == nullptr || ek[i] >= min_k);
-}
-
-__global__ void select_count_kernel(int64_t n, const uint32_t* ns, const uint32_t* ek, uint32_t min_n,
-                                    uint32_t min_k, int64_t* block_count) {
-    __shared__ int red[256];
-    const int64_t base = blockIdx.x * (int64_t)kSelPerBlock + threadIdx.x * 8;
-    int c = 0;
-    for (int j = 0; j < 8; ++j) c += row_selected(base + j, n, ns, ek, min_n, min_k);
-    red[threadIdx.x] = c;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
+// Which of rows base .. base + 7 are selected, one bit each; VEC: both arrays
+// are 16-byte aligned and read 16 bytes at a time.
+template <bool VEC>
+__device__ __forceinline__ uint32_t rows_selected(int64_t base, int64_t n, const uint32_t* ns, const uint32_t* ek,
+                                                  uint32_t min_n, uint32_t min_k) {
+    uint32_t f = 0;
+    if (VEC && base + 8 <= n) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint4 a = *reinterpret_cast<const uint4*>(ns + base + 4 * h);
+            uint4 e = make_uint4(min_k, min_k, min_k, min_k);
+            if (ek) e = *reinterpret_cast<const uint4*>(ek + base + 4 * h);
+            f |= (uint32_t)(a.x >= min_n && e.x >= min_k) << (4 * h);
+            f |= (uint32_t)(a.y >= min_n && e.y >= min_k) << (4 * h + 1);
+            f |= (uint32_t)(a.z >= min_n && e.z >= min_k) << (4 * h + 2);
+            f |= (uint32_t)(a.w >= min_n && e.w >= min_k) << (4 * h + 3);
+        }
+        return f;
     }
-    if (threadIdx.x == 0) block_count[blockIdx.x] = red[0];
+    for (int j = 0; j < 8; ++j)
+        if (base + j < n && ns[base + j] >= min_n && (ek == nullptr || ek[base + j] >= min_k)) f |= 1u << j;
+    return f;
 }
 
-__global__ void select_scan_kernel(int64_t nb, int64_t* block_count, int64_t* total) {
-    if (threadIdx.x != 0) return;
-    int64_t acc = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        const int64_t c = block_count[b];
-        block_count[b] = acc;
-        acc += c;
+// Inclusive prefix sum over a wave.
+__device__ __forceinline__ int wave_scan(int v) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(v, off);
+        if (lane_id() >= off) v += o;
     }
-    *total = acc;
+    return v;
 }
 
-__global__ void select_write_kernel(int64_t n, const uint32_t* ns, const uint32_t* ek, uint32_t min_n,
-                                    uint32_t min_k, const int64_t* block_offset, int64_t* rows) {
+template <bool VEC>
+__global__ __launch_bounds__(256) void select_count_kernel(int64_t n, const uint32_t* ns, const uint32_t* ek,
+                                                           uint32_t min_n, uint32_t min_k, int64_t* block_count) {
     __shared__ int wave_sum[4];
     const int64_t base = blockIdx.x * (int64_t)kSelPerBlock + threadIdx.x * 8;
-    bool f[8];
-    int c = 0;
-    for (int j = 0; j < 8; ++j) {
-        f[j] = row_selected(base + j, n, ns, ek, min_n, min_k);
-        c += f[j];
+    int c = __popc(rows_selected<VEC>(base, n, ns, ek, min_n, min_k));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+    if (lane_id() == 0) wave_sum[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) block_count[blockIdx.x] = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+}
+
+// Exclusive prefix of the blocks' counts and their total, by one block: each
+// thread adds up four consecutive counts, a scan over the threads, and the
+// total carried to the next 4096.  (One thread over 2048 counts: 216 us.)
+constexpr int kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void select_scan_kernel(int64_t nb, int64_t* block_count, int64_t* total) {
+    __shared__ int wave_sum[kScanThreads / 64];
+    int64_t carry = 0;
+    for (int64_t at = 0; at < nb; at += 4 * kScanThreads) {
+        const int64_t i = at + 4 * (int64_t)threadIdx.x;
+        int c[4], s = 0;  // a block counts at most 2048 rows: 4096 of them fit 32 bits
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[j] = i + j < nb ? (int)block_count[i + j] : 0;
+            s += c[j];
+        }
+        const int incl = wave_scan(s);
+        if (lane_id() == 63) wave_sum[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            before += w < (int)(threadIdx.x >> 6) ? wave_sum[w] : 0;
+            all += wave_sum[w];
+        }
+        int64_t p = carry + before + incl - s;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i + j < nb) block_count[i + j] = p;
+            p += c[j];
+        }
+        carry += all;
+        __syncthreads();
     }
-    // exclusive prefix of c over the block: within the wave, then across waves
-    int incl = c;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off);
-        if (lane_id() >= off) incl += v;
-    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
+// The block's rows go through LDS so that they are written in whole lines.
+template <bool VEC>
+__global__ __launch_bounds__(256) void select_write_kernel(int64_t n, const uint32_t* ns, const uint32_t* ek,
+                                                           uint32_t min_n, uint32_t min_k, const int64_t* block_offset,
+                                                           int64_t* rows) {
+    __shared__ int wave_sum[4];
+    __shared__ uint16_t kept[kSelPerBlock];
+    const int64_t first = blockIdx.x * (int64_t)kSelPerBlock;
+    const uint32_t f = rows_selected<VEC>(first + threadIdx.x * 8, n, ns, ek, min_n, min_k);
+    // exclusive prefix of the counts over the block: within the wave, then across waves
+    const int incl = wave_scan(__popc(f));
     const int wave = threadIdx.x >> 6;
     if (lane_id() == 63) wave_sum[wave] = incl;
     __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wave_sum[w];
-    int64_t pos = block_offset[blockIdx.x] + before + incl - c;
+    int pos = incl - __popc(f), all = 0;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) pos += wave_sum[w];
+        all += wave_sum[w];
+    }
     for (int j = 0; j < 8; ++j)
-        if (f[j]) rows[pos++] = base + j;
+        if ((f >> j) & 1u) kept[pos++] = (uint16_t)(threadIdx.x * 8 + j);
+    __syncthreads();
+    int64_t* dst = rows + block_offset[blockIdx.x];
+    for (int q = threadIdx.x; q < all; q += 256) dst[q] = first + kept[q];
 }
 
 // ---------------------------------------------------------------------------
 // FP64 column moments: deterministic two-pass (mean, then centred squares).
 
-constexpr int kMomBlocks = 256;
+constexpr int kMomBlocks = 1024, kMomMinBlocks = 256, kMomThreads = 256;
 
-__global__ void moments_partial_kernel(const float* x, int64_t n, int dim, const double* mean, double* partial) {
-    __shared__ double red[256][16];
-    double acc[16];
-    for (int k = 0; k < 16; ++k) acc[k] = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        for (int k = 0; k < dim; ++k) {
-            double v = (double)x[i * dim + k];
-            if (mean) {
-                v -= mean[k];
-                v *= v;
-            }
-            acc[k] += v;
+// Sums of the columns over this block's share of the matrix, read as one flat
+// array of V floats per thread (V = 4: 16-byte aligned).  The number of blocks
+// is a multiple of dim, so a thread meets the same columns in every round.
+// HBM-bound: 2.6e6 x 7 floats 50 -> 15 us (rows per thread and 256 blocks left
+// one wave per SIMD).
+template <int V>
+__global__ __launch_bounds__(kMomThreads) void moments_partial_kernel(const float* x, int64_t total, int dim,
+                                                                      const double* mean, double* partial) {
+    __shared__ double red[kMomThreads * V];
+    __shared__ double sums[16][17];
+    const int t = threadIdx.x;
+    const int64_t at = (blockIdx.x * (int64_t)kMomThreads + t) * V, stride = (int64_t)gridDim.x * kMomThreads * V;
+    double mu[V], acc[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        mu[j] = mean ? mean[(at + j) % dim] : 0.0;
+        acc[j] = 0.0;
+    }
+    auto add = [&](const float* p) __attribute__((always_inline)) {
+        float v[V];
+        if constexpr (V == 4) {
+            const float4 f = *reinterpret_cast<const float4*>(p);
+            v[0] = f.x;
+            v[1] = f.y;
+            v[2] = f.z;
+            v[3] = f.w;
+        } else {
+            v[0] = *p;
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const double d = (double)v[j] - mu[j];
+            acc[j] += mean ? d * d : d;
+        }
+    };
+#pragma unroll 4
+    for (int64_t p = at; p + V <= total; p += stride) add(x + p);
+#pragma unroll
+    for (int j = 0; j < V; ++j) red[t * V + j] = acc[j];
+    __syncthreads();
+    if (V > 1 && blockIdx.x == 0 && t == 0) {
+        // the matrix's last elements, fewer than V: entry e % dim of block 0
+        // is one of column e % dim
+        for (int64_t e = total - total % V; e < total; ++e) {
+            const int c = (int)(e % dim);
+            const double d = (double)x[e] - (mean ? mean[c] : 0.0);
+            red[c] += mean ? d * d : d;
         }
     }
-    for (int k = 0; k < 16; ++k) red[threadIdx.x][k] = acc[k];
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off)
-            for (int k = 0; k < dim; ++k) red[threadIdx.x][k] += red[threadIdx.x + off][k];
-        __syncthreads();
+    // column k = t % 16: entries k', k' + dim, ... of red, 16 threads each
+    const int k = t & 15, r = t >> 4;
+    double s = 0.0;
+    if (k < dim) {
+        const int off = (int)((blockIdx.x * (int64_t)kMomThreads * V) % dim);
+        const int e0 = k >= off ? k - off : k - off + dim;
+        for (int e = e0 + dim * r; e < kMomThreads * V; e += dim * 16) s += red[e];
     }
-    if (threadIdx.x < dim) partial[blockIdx.x * 16 + threadIdx.x] = red[0][threadIdx.x];
+    sums[k][r] = s;
+    __syncthreads();
+    if (t < 16) {
+        s = 0.0;
+        for (int q = 0; q < 16; ++q) s += sums[t][q];
+        partial[blockIdx.x * 16 + t] = s;
+    }
 }
 
-__global__ void moments_final_kernel(const double* partial, int nblocks, int64_t n, int dim, double* out,
-                                     int second_pass) {
-    const int k = threadIdx.x;
-    if (k >= dim) return;
+__global__ __launch_bounds__(256) void moments_final_kernel(const double* partial, int nblocks, int64_t n, int dim,
+                                                            double* out, int second_pass) {
+    __shared__ double sums[16][17];
+    const int k = threadIdx.x & 15, r = threadIdx.x >> 4;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += partial[b * 16 + k];
-    if (!second_pass) out[k] = s / (double)n;
-    else out[16 + k] = sqrt(s / (double)n);
+#pragma unroll 8
+    for (int b = r; b < nblocks; b += 16) s += partial[b * 16 + k];
+    sums[k][r] = s;
+    __syncthreads();
+    if ((int)threadIdx.x >= dim) return;
+    s = 0.0;
+    for (int q = 0; q < 16; ++q) s += sums[threadIdx.x][q];
+    if (!second_pass) out[threadIdx.x] = s / (double)n;
+    else out[16 + threadIdx.x] = sqrt(s / (double)n);
 }
 
 // ---------------------------------------------------------------------------
@@ -967,11 +1091,14 @@ ms_status cvae_features(int32_t model, int64_t n, const int64_t* rows_dev, int64
     int cus;
     ms_status st = device_cu_count(&cus);
     if (st != MS_OK) return st;
-    int64_t blocks = (n + 255) / 256;
+    int64_t blocks = (n + kFeatThreads - 1) / kFeatThreads;
     if (blocks > cus * 8) blocks = cus * 8;
-    hipLaunchKernelGGL(cvae_features_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, model, n,
-                       rows_dev, n_records, params3_dev, n_scatter_dev, exit_param_dev, event_pos_dev, event_dir_dev,
-                       seed, id_offset, stats_dev, cond_dev, target_dev);
+    const auto kernel = model == MS_MODEL_LENGTH ? cvae_features_kernel<MS_MODEL_LENGTH>
+                        : model == MS_MODEL_PATH ? cvae_features_kernel<MS_MODEL_PATH>
+                                                 : cvae_features_kernel<MS_MODEL_EVENT>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kFeatThreads), 0, (hipStream_t)stream, n, rows_dev,
+                       n_records, params3_dev, n_scatter_dev, exit_param_dev, event_pos_dev, event_dir_dev, seed,
+                       id_offset, stats_dev, cond_dev, target_dev);
     MS_LAUNCHED();
     clear_error();
     return MS_OK;
@@ -998,11 +1125,12 @@ ms_status ms_select_rows(int64_t n, const uint32_t* n_scatter_dev, const uint32_
     const int64_t nb = (n + kSelPerBlock - 1) / kSelPerBlock;
     int64_t* bc = reinterpret_cast<int64_t*>(workspace_dev);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(select_count_kernel, dim3((unsigned)nb), dim3(256), 0, s, n, n_scatter_dev, event_index_dev,
-                       min_scatter, min_event, bc);
-    hipLaunchKernelGGL(select_scan_kernel, dim3(1), dim3(64), 0, s, nb, bc, count_dev);
-    hipLaunchKernelGGL(select_write_kernel, dim3((unsigned)nb), dim3(256), 0, s, n, n_scatter_dev, event_index_dev,
-                       min_scatter, min_event, (const int64_t*)bc, rows_dev);
+    const bool vec = (((uintptr_t)n_scatter_dev | (uintptr_t)event_index_dev) & 15u) == 0;
+    hipLaunchKernelGGL(vec ? select_count_kernel<true> : select_count_kernel<false>, dim3((unsigned)nb), dim3(256), 0, s,
+                       n, n_scatter_dev, event_index_dev, min_scatter, min_event, bc);
+    hipLaunchKernelGGL(select_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, nb, bc, count_dev);
+    hipLaunchKernelGGL(vec ? select_write_kernel<true> : select_write_kernel<false>, dim3((unsigned)nb), dim3(256), 0, s,
+                       n, n_scatter_dev, event_index_dev, min_scatter, min_event, (const int64_t*)bc, rows_dev);
     MS_LAUNCHED();
     clear_error();
     return MS_OK;
@@ -1020,19 +1148,27 @@ ms_status ms_column_moments(const float* x_dev, int64_t n, int32_t dim, double* 
     MS_REQUIRE(x_dev && out_dev, "ms_column_moments: NULL array");
     MS_REQUIRE(n > 0 && dim >= 1 && dim <= 16, "ms_column_moments: need n > 0 and 1 <= dim <= 16");
     MS_REQUIRE(workspace_dev != nullptr, "ms_column_moments: workspace is NULL");
-    if (workspace_bytes < (size_t)kMomBlocks * 16 * sizeof(double))
+    if (workspace_bytes < (size_t)kMomMinBlocks * 16 * sizeof(double))
         return set_error(MS_ERR_WORKSPACE_TOO_SMALL, "ms_column_moments: workspace too small");
     int cus;
     ms_status st = device_cu_count(&cus);
     if (st != MS_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     double* partial = reinterpret_cast<double*>(workspace_dev);
-    hipLaunchKernelGGL(moments_partial_kernel, dim3(kMomBlocks), dim3(256), 0, s, x_dev, n, dim, (const double*)nullptr,
-                       partial);
-    hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(64), 0, s, partial, kMomBlocks, n, dim, out_dev, 0);
-    hipLaunchKernelGGL(moments_partial_kernel, dim3(kMomBlocks), dim3(256), 0, s, x_dev, n, dim, (const double*)out_dev,
-                       partial);
-    hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(64), 0, s, partial, kMomBlocks, n, dim, out_dev, 1);
+    const int64_t total = n * dim;
+    const bool vec = ((uintptr_t)x_dev & 15u) == 0;
+    const auto sums = vec ? moments_partial_kernel<4> : moments_partial_kernel<1>;
+    // a multiple of dim, no more than the matrix fills or the workspace holds
+    int64_t fill = (total + kMomThreads * 4 - 1) / (kMomThreads * 4);
+    const int64_t room = (int64_t)(workspace_bytes / (16 * sizeof(double)));
+    if (fill > kMomBlocks) fill = kMomBlocks;
+    if (fill > room) fill = room;
+    const int nb = (int)(fill / dim > 0 ? fill / dim : 1) * dim;
+    for (int pass = 0; pass < 2; ++pass) {
+        hipLaunchKernelGGL(sums, dim3(nb), dim3(kMomThreads), 0, s, x_dev, total, dim,
+                           pass ? (const double*)out_dev : nullptr, partial);
+        hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(256), 0, s, (const double*)partial, nb, n, dim, out_dev, pass);
+    }
     MS_LAUNCHED();
     clear_error();
     return MS_OK;

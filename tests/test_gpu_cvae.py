@@ -81,6 +81,63 @@ def test_select_rows_is_exact(msst):
     assert rows.size == 0
 
 
+@pytest.mark.parametrize("n", [1, 7, 8, 2047, 2049, 100003, 4096 * 2048 + 4099])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_select_rows_at_block_edges_and_unaligned(msst, n, offset):
+    """Fewer rows than a thread's eight, remainders of a block's 2048, more
+    blocks than the scan takes at once (4096), and arrays that are not
+    16-byte aligned."""
+    announce(f"select rows n={n} offset={offset}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    ns = torch.randint(1, 5, (n + offset,), generator=g, device="cuda", dtype=torch.int32)[offset:]
+    ek = torch.randint(1, 4, (n + offset,), generator=g, device="cuda", dtype=torch.int32)[offset:]
+    walk = dict(n_scatter=ns, event_index=ek)
+    assert torch.equal(msst.select_rows(walk, 2), (ns >= 2).nonzero().reshape(-1))
+    assert torch.equal(msst.select_rows(walk, 3, 2), ((ns >= 3) & (ek >= 2)).nonzero().reshape(-1))
+
+
+@pytest.mark.parametrize("dim", [1, 2, 3, 5, 6, 7, 12, 16])
+@pytest.mark.parametrize("n,offset", [(1, 0), (5, 0), (341, 1), (100001, 0), (100002, 3)])
+def test_column_moments_of_any_width(msst, dim, n, offset):
+    """FP64 sums of n terms in any order agree to n 2^-53 relative of the sum
+    of magnitudes (1e-11 at n = 10^5), over remainders of four elements and
+    unaligned matrices, with the smallest workspace accepted and the default."""
+    announce(f"column moments dim={dim} n={n} offset={offset}")
+    g = torch.Generator(device="cuda").manual_seed(dim * n)
+    x = (torch.randn(n * dim + offset, generator=g, device="cuda") + 3.0)[offset:].view(n, dim)
+    ref = x.double().cpu().numpy()
+    for ws_bytes in (256 * 16 * 8, msst.ms_column_moments_workspace_size(n, dim)):
+        out = torch.zeros(32, dtype=torch.float64, device="cuda")
+        msst.ms_column_moments(x, n, dim, out, torch.empty(ws_bytes, dtype=torch.uint8, device="cuda"))
+        o = out.cpu().numpy()
+        np.testing.assert_allclose(o[:dim], ref.mean(0), rtol=1e-11)
+        np.testing.assert_allclose(o[16:16 + dim], ref.std(0), rtol=1e-11, atol=1e-11)
+
+
+@pytest.mark.parametrize("model", MODELS)
+@pytest.mark.parametrize("n", [1, 255, 257, 3000])
+def test_features_of_selected_rows_standardised(msst, model, n):
+    """Rows in any order and blocks with a remainder; a column without spread
+    divides by zero as FP64 does (0/0, x/0), the others round the FP64 quotient
+    to binary32 once: 2^-24 relative, and logf's 1 ulp of the conditions."""
+    announce(f"features model={model} n={n}")
+    walk = msst.random_walk(4000, seed=8, mode=1)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rows = torch.randint(0, 4000, (n,), generator=g, device="cuda")
+    p_in, p_out = [(2, 1), (3, 3), (7, 6)][model]
+    raw_c, raw_y = torch.empty((n, p_in), device="cuda"), torch.empty((n, p_out), device="cuda")
+    msst.cvae_features(model, n, walk, 4, 0, None, raw_c, raw_y, rows=rows)
+    st = torch.rand(64, generator=g, device="cuda", dtype=torch.float64) + 0.25
+    st[17] = 0.0
+    c, y = torch.empty_like(raw_c), torch.empty_like(raw_y)
+    msst.cvae_features(model, n, walk, 4, 0, st, c, y, rows=rows)
+    ref_c = (raw_c.double() - st[:p_in]) / st[16:16 + p_in]
+    ref_y = (raw_y.double() - st[32:32 + p_out]) / st[48:48 + p_out]
+    np.testing.assert_allclose(c.cpu().numpy(), ref_c.float().cpu().numpy(), rtol=1.2e-7)
+    np.testing.assert_allclose(y.cpu().numpy(), ref_y.float().cpu().numpy(), rtol=1.2e-7)
+    assert not torch.isfinite(c[:, 1]).any()
+
+
 def grad_case(msst, oracle, model, B, sample_rows=0, n_rows=None, kl_weight=1.0):
     shape = W.SHAPE_LIST[model]
     master64 = oracle.cvae_init(shape, seed=31 + model).astype(np.float32).astype(np.float64)
