@@ -108,22 +108,40 @@ __device__ __forceinline__ void box_muller(float ua, float ub, float& n0, float&
 struct HgSample {
     float mu, sin_t;
 };
-__device__ __forceinline__ HgSample hg_sample(float g, float xi) {
-    const float q = __builtin_fmaf(g, 2.0f * xi - 1.0f, 1.0f);
+// What a medium's asymmetry g alone decides of the phase function: one medium
+// per launch or photon, so its loops hold these and no more arithmetic on g.
+struct Hg {
+    float g, omg, om2, op2;     // g, 1 - g, 2 (1 - g)^2, 2 (1 + g)^2
+    float eval_c, eval_a, eval_b;  // (1 - g^2) / 4 pi, -2 g, 1 + g^2
+};
+__host__ __device__ __forceinline__ Hg hg_const(float g) {
+    Hg h;
+    h.g = g;
+    h.omg = 1.0f - g;
+    const float opg = 1.0f + g;
+    h.om2 = 2.0f * h.omg * h.omg;
+    h.op2 = 2.0f * opg * opg;
+    h.eval_c = 0.0795774715459476679f * __builtin_fmaf(-g, g, 1.0f);
+    h.eval_a = -2.0f * g;
+    h.eval_b = __builtin_fmaf(g, g, 1.0f);
+    return h;
+}
+__device__ __forceinline__ HgSample hg_sample(const Hg& c, float xi) {
+    const float q = __builtin_fmaf(c.g, __builtin_fmaf(xi, 2.0f, -1.0f), 1.0f);
     const float iq2 = fast_rcp(q * q);
-    const float omg = 1.0f - g, opg = 1.0f + g;
-    const float om = 2.0f * omg * omg * (1.0f - xi) * __builtin_fmaf(g, xi, 1.0f) * iq2;
-    const float op = 2.0f * opg * opg * xi * __builtin_fmaf(g, xi, omg) * iq2;
+    const float om = c.om2 * (1.0f - xi) * __builtin_fmaf(c.g, xi, 1.0f) * iq2;
+    const float opq = c.op2 * xi * __builtin_fmaf(c.g, xi, c.omg);
+    const float op = opq * iq2;
     HgSample h;
-    h.mu = __builtin_fminf(1.0f, __builtin_fmaxf(-1.0f, 0.5f * (op - om)));
+    h.mu = __builtin_fminf(1.0f, __builtin_fmaxf(-1.0f, 0.5f * __builtin_fmaf(opq, iq2, -om)));
     h.sin_t = fast_sqrt(__builtin_fminf(1.0f, om * op));
     return h;
 }
 
 // HG phase function value (Eq. 1).
-__device__ __forceinline__ float hg_eval(float g, float cos_t) {
-    const float den = __builtin_fmaf(-2.0f * g, cos_t, 1.0f + g * g);
-    return 0.0795774715459476679f * (1.0f - g * g) * fast_rsq(den) * fast_rcp(den);
+__device__ __forceinline__ float hg_eval(const Hg& c, float cos_t) {
+    const float den = __builtin_fmaf(c.eval_a, cos_t, c.eval_b);
+    return c.eval_c * fast_rsq(den) * fast_rcp(den);
 }
 
 struct V3 {
@@ -222,10 +240,10 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 struct TicketPool {
     uint64_t next, end;
     bool dry;
-    __device__ __forceinline__ void reset(uint64_t wave, uint32_t chunk) {
+    __device__ __forceinline__ void reset(uint64_t wave, uint64_t waves, uint32_t chunk, uint64_t n) {
         next = wave * chunk;
         end = next + chunk;
-        dry = false;
+        dry = waves * chunk >= n;
     }
     // Returns this lane's ticket (meaningful where `need`): work for it below n.
     __device__ __forceinline__ uint64_t take(bool need, unsigned long long* counter, uint32_t chunk, uint64_t n) {

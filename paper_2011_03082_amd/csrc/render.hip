@@ -24,7 +24,6 @@
 namespace msst {
 
 constexpr int kRenderWaves = 4;
-constexpr uint32_t kTickets = 64;  // work units a wave takes at a time
 
 // Lane states: no path in flight (NEED: start a sample, take a work unit,
 // or wait for the parked path), tracing (FLY), waiting for a learned step
@@ -65,7 +64,8 @@ struct RenderArgs {
     uint32_t surv_thr;
     int method, sampler;
     const PackedModel* pm[3];
-    float tau_min, st_max, min_chain;
+    float tau_min, r_cap, min_chain;  // r_cap = st_max / sigma_t
+    Hg hg;
     int spp, chunk, n_chunks;
     int64_t n_units;                      // below 2^32
     double inv_n_chunks, inv_width;       // reciprocals for the unit -> (pixel, chunk) split
@@ -76,10 +76,30 @@ struct RenderArgs {
     int max_wait;
     int nee_samples, nee_chain;
     int flags;
+    int lanes;         // lanes of a wave that take work units, as many at a time
+    int gated;         // ticket[2] says whether the plain kernel or the sphere tracer runs
     UnitRecord* part;  // [n_units], unit = pixel * n_chunks + chunk
     unsigned long long* ticket;
     unsigned long long* counters;
 };
+
+// The launch's arguments (the kernels' only parameter), loaded where they are
+// read instead of once before the loops.  What only the restarts read, and the
+// constants of the phase function, kept in registers -- and with the camera
+// every interval test's share of it, computed ahead of the loop -- pushed others
+// out of the 100 scalar and, at four waves per SIMD, 128 vector registers: the
+// learned C4 image 15.6 -> 14.6 ms (no vector spills are left, and 63 instead
+// of 118 scalar ones), the plain one 13.8 -> 13.3 ms.
+typedef const __attribute__((address_space(4))) RenderArgs* ColdArgs;
+__device__ __forceinline__ ColdArgs cold_args() {
+    ColdArgs c = (ColdArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(c));
+    return c;
+}
+__device__ __forceinline__ Hg cold_hg() {
+    const ColdArgs c = cold_args();
+    return Hg{c->hg.g, c->hg.omg, c->hg.om2, c->hg.op2, c->hg.eval_c, c->hg.eval_a, c->hg.eval_b};
+}
 
 // Primitives held in registers for the whole kernel (NP slots).
 template <int NP>
@@ -95,6 +115,21 @@ struct RenderLds {
 };
 
 enum : int { kModePlain = 0, kModeStExact = 1, kModeStCvae = 2 };
+
+// Paths a wave has left, with no work units to take, when it starts to trace
+// them together (four lanes or more for each).
+constexpr int kTraceTogether = 16;
+
+// The next G flights of each of 64 / G paths traced together, a padding entry
+// after each path's.
+struct alignas(16) TogetherLds {
+    float4 turn[80];    // drawn: mu, sin theta, cosine and sine of the azimuth
+    float4 pos[80];     // collision at the end of the flight
+    float4 dir[80];     // direction of the flight
+    float flight[80];   // drawn: its length
+    float light[80];    // direct light at the collision (0: none there)
+    uint32_t lane[64];  // lane that holds the k-th live path
+};
 
 // Events of one exact walk inside a sphere before it is cut off (the reference
 // sampler; a sphere of optical radius 200 takes about 10^5 on average).
@@ -235,7 +270,7 @@ __device__ __forceinline__ float nee(const RenderArgs& A, const Prims<NP>& P, V3
             t = dist;
         }
     }
-    return A.intensity * hg_eval(A.g, dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
+    return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
 }
 
 // ---------------------------------------------------------------- geometry policies
@@ -264,20 +299,6 @@ struct Geo {
         for (int i = 0; i < NP; ++i)
             if (i < P.n) s = __builtin_fminf(s, prim_depth(P.p[i], p));
         return union_radius(s);
-    }
-    // An upper bound of radius() over the whole scene: union_radius of the
-    // deepest point of the deepest primitive (a sphere's centre at depth r, a
-    // box's at its smallest half size), in the same rounding; unbounded with
-    // a grid.
-    __device__ __forceinline__ float max_radius() const {
-        if (GRID) return INFINITY;
-        float m = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NP; ++i)
-            if (i < P.n)
-                m = __builtin_fmaxf(m, P.p[i][0] == 0.0f ? P.p[i][4]
-                                                         : __builtin_fminf(P.p[i][4], __builtin_fminf(P.p[i][5], P.p[i][6])));
-        return union_radius(-m);
     }
     __device__ __forceinline__ float flight_bound(const RenderArgs&, V3) const { return 0.0f; }
     __device__ __forceinline__ float light(const RenderArgs& A, V3 x, V3 d) const { return nee(A, P, x, d); }
@@ -351,7 +372,6 @@ struct GeoMany {
         return union_radius(sd);
     }
     __device__ __forceinline__ float flight_bound(const RenderArgs& A, V3 p) const { return radius(A, p); }
-    __device__ __forceinline__ float max_radius() const { return INFINITY; }
 
     // Primitives the shadow segments of this wave can meet.  Called by every
     // lane of the wave (converged); lanes with `active` will trace a segment
@@ -475,7 +495,7 @@ struct GeoMany {
                 t = pe;
             }
         }
-        return A.intensity * hg_eval(A.g, dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
+        return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
     }
 };
 
@@ -511,7 +531,6 @@ struct GeoMesh {
     }
     __device__ __forceinline__ bool piece(V3, V3, float t, float& s, float& e) const { return union_piece(iv, t, s, e); }
     __device__ __forceinline__ float radius(const RenderArgs& A, V3 p) const { return grid_radius(A, p); }
-    __device__ __forceinline__ float max_radius() const { return INFINITY; }
     __device__ __forceinline__ float flight_bound(const RenderArgs&, V3) const { return 0.0f; }
 
     __device__ __forceinline__ float light(const RenderArgs& A, V3 x, V3 d) const {
@@ -531,7 +550,7 @@ struct GeoMesh {
                 prev = c[k];
             }
         if ((m & 1) == 0) acc += dist - prev;
-        return A.intensity * hg_eval(A.g, dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
+        return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
     }
 };
 constexpr int kGeoMesh = 8;  // render_kernel template tag of mesh scenes
@@ -716,14 +735,16 @@ __device__ __forceinline__ int wave_prefix_small(int cnt, int& total) {
 // samples of its work unit one after the other and banks them in order.
 template <int MODE, int NP, bool GRID>
 __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, const float* lds_prims,
-                                            uint32_t (*tot)[64 * kRenderWaves], BlockTotals& totals) {
+                                            uint32_t (*tot)[64 * kRenderWaves], BlockTotals& totals,
+                                            TogetherLds& T) {
     typename GeoSel<NP, GRID>::type G;
     constexpr bool kWaveLight = GeoSel<NP, GRID>::type::kWaveLight;
     G.init(A, lds_prims);
 
     TicketPool pool;
-    pool.reset((uint64_t)blockIdx.x * kRenderWaves + (threadIdx.x >> 6), kTickets);
-    int state = S_NEED;
+    pool.reset((uint64_t)blockIdx.x * kRenderWaves + uniform_u32(threadIdx.x >> 6), (uint64_t)gridDim.x * kRenderWaves, A.lanes,
+               (uint64_t)A.n_units);
+    int state = lane_id() < A.lanes ? S_NEED : S_DONE;
     // current path
     Rng rng = make_rng(A.seed, MS_TAG_RENDER_PATH, 0);
     V3 o = v3(0, 0, 0), d = v3(0, 0, 1);
@@ -742,20 +763,24 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     for (int q = 0; q < kLaneWords; ++q) tot[q][tid] = 0;
     tot[U_UNIT][tid] = U_NONE;
 
-    auto start_path = [&](uint32_t pixel, int q) __attribute__((always_inline)) {
-        const int py = (int)udiv_exact(pixel, (uint32_t)A.width, A.inv_width);
-        const int px = (int)pixel - py * A.width;
-        const uint64_t sample = A.sample_offset + (uint64_t)q;
+    auto begin_path = [&](uint32_t pixel, int q) __attribute__((always_inline)) {
+        const ColdArgs C = cold_args();
+        const int py = (int)udiv_exact(pixel, (uint32_t)C->width, C->inv_width);
+        const int px = (int)pixel - py * C->width;
+        const uint64_t sample = C->sample_offset + (uint64_t)q;
         const uint64_t id = (uint64_t)pixel | (sample << 32);
-        const Rng rp = make_rng(A.seed, MS_TAG_RENDER_PIXEL, id);
+        const Rng rp = make_rng(C->seed, MS_TAG_RENDER_PIXEL, id);
         const uint4 jw = rp.block(0);
-        rng = make_rng(A.seed, MS_TAG_RENDER_PATH, id);
-        const float sx = 2.0f * ((float)px + u01(jw.x)) / (float)A.width - 1.0f;
-        const float sy = 1.0f - 2.0f * ((float)py + u01(jw.y)) / (float)A.height;
-        o = v3(A.eye[0], A.eye[1], A.eye[2]);
-        d = normalize(v3(A.fwd[0] + sx * A.right[0] + sy * A.upv[0], A.fwd[1] + sx * A.right[1] + sy * A.upv[1],
-                         A.fwd[2] + sx * A.right[2] + sy * A.upv[2]));
-        G.set_camera_ray(o, d);
+        // the key and the tag stay as they are: uniform, in scalar registers
+        const Rng fresh = make_rng(C->seed, MS_TAG_RENDER_PATH, id);
+        rng.s0 = fresh.s0;
+        rng.s1 = fresh.s1;
+        rng.s2 = fresh.s2;
+        const float sx = 2.0f * ((float)px + u01(jw.x)) / (float)C->width - 1.0f;
+        const float sy = 1.0f - 2.0f * ((float)py + u01(jw.y)) / (float)C->height;
+        o = v3(C->eye[0], C->eye[1], C->eye[2]);
+        d = normalize(v3(C->fwd[0] + sx * C->right[0] + sy * C->upv[0], C->fwd[1] + sx * C->right[1] + sy * C->upv[1],
+                         C->fwd[2] + sx * C->right[2] + sy * C->upv[2]));
         t = 0.0f;
         Lp = 0.0f;
         c0 = 0;
@@ -775,47 +800,57 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         end_age = rmask != 0 ? end_age + 1 : 0;
         return rmask != 0 && (__popcll(rmask) >= A.restart_min || amask == 0 || end_age > A.max_wait);
     };
-    auto restart = [&]() __attribute__((always_inline)) {
-        end_age = 0;
-        bool start = false;
-        int s_next = 0;
-        if (state == S_END) {
-            float acc_sum = __uint_as_float(tot[U_SUM][tid]), acc_comp = __uint_as_float(tot[U_COMP][tid]);
-            neumaier_add(acc_sum, acc_comp, Lp);
-            const float acc_sq = __builtin_fmaf(Lp, Lp, __uint_as_float(tot[U_SQ][tid]));
-            const uint32_t acc_ev = tot[U_EV][tid] + p_ev, acc_st = tot[U_ST][tid] + p_st;
-            s_next = (int)tot[U_NEXT][tid];
-            if (s_next < (int)tot[U_END][tid]) {
-                tot[U_SUM][tid] = __float_as_uint(acc_sum);
-                tot[U_COMP][tid] = __float_as_uint(acc_comp);
-                tot[U_SQ][tid] = __float_as_uint(acc_sq);
-                tot[U_EV][tid] = acc_ev;
-                tot[U_ST][tid] = acc_st;
-                start = true;
+    // Banks the finished path into its work unit (the LDS words of thread
+    // `home`, written by one lane: `writer`); returns the unit's next sample,
+    // or -1 after its last one, when the unit's record is written.
+    auto bank = [&](int home, bool writer) __attribute__((always_inline)) -> int {
+        float acc_sum = __uint_as_float(tot[U_SUM][home]), acc_comp = __uint_as_float(tot[U_COMP][home]);
+        neumaier_add(acc_sum, acc_comp, Lp);
+        const float acc_sq = __builtin_fmaf(Lp, Lp, __uint_as_float(tot[U_SQ][home]));
+        const uint32_t acc_ev = tot[U_EV][home] + p_ev, acc_st = tot[U_ST][home] + p_st;
+        const int s_next = (int)tot[U_NEXT][home];
+        const bool more = s_next < (int)tot[U_END][home];
+        if (writer) {
+            if (more) {
+                tot[U_SUM][home] = __float_as_uint(acc_sum);
+                tot[U_COMP][home] = __float_as_uint(acc_comp);
+                tot[U_SQ][home] = __float_as_uint(acc_sq);
+                tot[U_EV][home] = acc_ev;
+                tot[U_ST][home] = acc_st;
             } else {
-                // the unit's last sample: its record
                 UnitRecord rec;
                 rec.sum = acc_sum + acc_comp;
                 rec.sumsq = acc_sq;
                 rec.events = acc_ev;
                 rec.steps = acc_st;
-                A.part[tot[U_UNIT][tid]] = rec;
-                tot[T_EVENTS][tid] += acc_ev;
-                tot[T_STEPS][tid] += acc_st;
-                tot[U_UNIT][tid] = U_NONE;
+                cold_args()->part[tot[U_UNIT][home]] = rec;
+                tot[T_EVENTS][home] += acc_ev;
+                tot[T_STEPS][home] += acc_st;
+                tot[U_UNIT][home] = U_NONE;
             }
+        }
+        return more ? s_next : -1;
+    };
+    auto restart = [&]() __attribute__((always_inline)) {
+        end_age = 0;
+        const ColdArgs C = cold_args();
+        bool start = false;
+        int s_next = 0;
+        if (state == S_END) {
+            s_next = bank(tid, true);
+            start = s_next >= 0;
             state = S_NEED;
         }
         const bool need = state == S_NEED && tot[U_UNIT][tid] == U_NONE;
-        const uint64_t tk = pool.take(need, A.ticket, kTickets, (uint64_t)A.n_units);
+        const uint64_t tk = pool.take(need, C->ticket, C->lanes, (uint64_t)C->n_units);
         if (need) {
-            if (tk < (uint64_t)A.n_units) {
+            if (tk < (uint64_t)C->n_units) {
                 tot[U_UNIT][tid] = (uint32_t)tk;
                 // pixel-major: a wave's block of tickets covers few pixels
-                const uint32_t pixel = udiv_exact((uint32_t)tk, (uint32_t)A.n_chunks, A.inv_n_chunks);
-                const int ch = (int)((uint32_t)tk - pixel * (uint32_t)A.n_chunks);
-                s_next = ch * A.chunk;
-                tot[U_END][tid] = (uint32_t)(s_next + A.chunk < A.spp ? s_next + A.chunk : A.spp);
+                const uint32_t pixel = udiv_exact((uint32_t)tk, (uint32_t)C->n_chunks, C->inv_n_chunks);
+                const int ch = (int)((uint32_t)tk - pixel * (uint32_t)C->n_chunks);
+                s_next = ch * C->chunk;
+                tot[U_END][tid] = (uint32_t)(s_next + C->chunk < C->spp ? s_next + C->chunk : C->spp);
                 tot[U_SUM][tid] = tot[U_COMP][tid] = tot[U_SQ][tid] = 0u;
                 tot[U_EV][tid] = tot[U_ST][tid] = 0u;
                 start = true;
@@ -825,7 +860,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         }
         if (start) {
             const uint32_t unit = tot[U_UNIT][tid];
-            start_path(udiv_exact(unit, (uint32_t)A.n_chunks, A.inv_n_chunks), s_next);
+            begin_path(udiv_exact(unit, (uint32_t)C->n_chunks, C->inv_n_chunks), s_next);
+            G.set_camera_ray(o, d);
             tot[U_NEXT][tid] = (uint32_t)(s_next + 1);
         }
     };
@@ -862,7 +898,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     } else {
                         bool plain = true;
                         if (MODE != kModePlain) {
-                            const float r = __builtin_fminf(G.radius(A, p), A.st_max * A.inv_sigma_t);
+                            const float r = __builtin_fminf(G.radius(A, p), A.r_cap);
                             if (A.sigma_t * r >= A.tau_min) {
                                 plain = false;
                                 if (MODE == kModeStExact) {
@@ -883,7 +919,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                                             Xk = x;
                                             Wk = dir;
                                         }
-                                        const HgSample h = hg_sample(A.g, u01(ww.y));
+                                        const HgSample h = hg_sample(cold_hg(), u01(ww.y));
                                         dir = scatter(dir, h.mu, h.sin_t, u01(ww.z));
                                         const float ll = -flight_ln(u01(ww.x)) * A.inv_sigma_t;
                                         const V3 rel = x - p;
@@ -925,7 +961,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                             if (u24(w.w) > A.surv_thr) {
                                 path_end = true;
                             } else {
-                                const HgSample h = hg_sample(A.g, u01(w.y));
+                                const HgSample h = hg_sample(cold_hg(), u01(w.y));
                                 d = scatter(d, h.mu, h.sin_t, u01(w.z));
                                 o = p;
                                 G.set_ray(o, d);
@@ -1008,7 +1044,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         };
         const float w_nee = (before ? lam : lambda_weight(A, N)) / (float)events_of(N);
         float ct = 0.0f, al = 0.0f, be = 0.0f, ga = 1.0f;
-        if (lit && !use_path) ct = hg_sample(A.g, u_hg).mu;
+        if (lit && !use_path) ct = hg_sample(cold_hg(), u_hg).mu;
         const uint64_t pmask = ballot(use_path);
         const float lnN = fast_ln(N);
         if (pmask) {
@@ -1142,6 +1178,219 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             }
         }
     };
+    // The last paths of a wave, traced together.  With few paths left, or few
+    // in the whole launch, a path is a chain of collisions on a lane of its
+    // own, 450 instructions each, and the wave issues them whatever lanes are
+    // idle.  But only the turn of the direction depends on the collision
+    // before: here a path has G = 64 / (paths left) lanes, which draw its next
+    // G flights, follow them as if none left the body (all lanes the same,
+    // about 40 instructions a collision), and then each check one of them
+    // against the boundary and trace its shadow ray.  The path goes on from the
+    // first flight that did leave, or ends where it was absorbed; the light
+    // is added up in the order of the collisions, as one lane does.  (Bound by
+    // the issue of one wave, an instruction every 6 cycles; meshes by the
+    // latency of the traversals, now G at a time.)  A 99 x 75 x 4 preview of
+    // the sphere and box 650 -> 157 us, of a mesh 8.4 -> 1.6 ms; the 512^2 x 256
+    // image's last paths 15.5 -> 13.8 ms.
+    auto trace_together = [&]() __attribute__((always_inline)) {
+        const int lane = lane_id();
+        int home = tid;
+        bool live = state == S_FLY, leader = true;
+        for (uint64_t left = ballot(live); left != 0; left = ballot(live && leader)) {
+            const int n_live = __popcll(left);
+            const int lg = n_live > 1 ? 6 - (32 - __builtin_clz((uint32_t)(n_live - 1))) : 6;
+            const int GL = 1 << lg, chain = lane >> lg, slot0 = chain * (GL + 1), mine = lane & (GL - 1);
+            if (live && leader) T.lane[rank_in(left)] = (uint32_t)lane;
+            wave_sync();
+            const int src = (int)T.lane[chain < n_live ? chain : 0];
+            wave_sync();
+            auto from = [src](uint32_t v) __attribute__((always_inline)) { return (uint32_t)__shfl((int)v, src); };
+            auto fromf = [src](float v) __attribute__((always_inline)) { return __shfl(v, src); };
+            rng.s0 = from(rng.s0);
+            rng.s1 = from(rng.s1);
+            rng.s2 = from(rng.s2);
+            c0 = from(c0);
+            p_ev = from(p_ev);
+            home = (int)from((uint32_t)home);
+            o = v3(fromf(o.x), fromf(o.y), fromf(o.z));
+            d = v3(fromf(d.x), fromf(d.y), fromf(d.z));
+            t = fromf(t);
+            Lp = fromf(Lp);
+            live = chain < n_live;
+            leader = mine == 0;
+            const uint64_t my_bits = (lg == 6 ? ~0ull : (1ull << GL) - 1) << (chain << lg & 63);
+            int n_now = n_live;
+            bool redo = false;  // the next flight does not end where following it would
+            do {
+                const uint4 w = rng.block(c0 + (uint32_t)mine);
+                const HgSample h = hg_sample(cold_hg(), u01(w.y));
+                const float az = u01(w.z), l_mine = -flight_ln(u01(w.x)) * A.inv_sigma_t;
+                const uint64_t absorbed = ballot(u24(w.w) > A.surv_thr);
+                T.turn[slot0 + mine] = make_float4(h.mu, h.sin_t, cos_rev(az), sin_rev(az));
+                T.flight[slot0 + mine] = l_mine;
+                T.light[slot0 + mine] = 0.0f;
+                wave_sync();
+                // A flight of the ray (o, d) from t: its end in t; 0 in the
+                // medium, 1 at the boundary, 2 if the ray leaves for good.
+                auto fly = [&](V3 fo, V3 fd, float& ft, float l, bool camera) __attribute__((always_inline)) -> int {
+                    if (camera) G.set_camera_ray(fo, fd);
+                    else G.set_ray(fo, fd);
+                    float ps = ft, pe = INFINITY;
+                    const bool inside = l < G.flight_bound(A, fma3(ft, fd, fo));
+                    if (!inside && !G.piece(fo, fd, ft, ps, pe)) return 2;
+                    ft = __builtin_fmaxf(ft, ps);
+                    if (ft + l >= pe) {
+                        ft = pe;
+                        return 1;
+                    }
+                    ft += l;
+                    return 0;
+                };
+                bool ended = false, truncated = false;
+                uint32_t e0 = 0;
+                // Flights that do not start at a collision (camera rays, rays
+                // going on from the boundary), and at the event limit.
+                for (;;) {
+                    const bool exact = live && !ended && e0 < (uint32_t)GL && (redo || t != 0.0f || p_ev == 0u || p_ev >= A.max_events);
+                    if (ballot(exact) == 0) break;
+                    if (exact) {
+                        redo = false;
+                        const int at = slot0 + (int)e0;
+                        const int out = fly(o, d, t, T.flight[at], p_ev == 0u);
+                        if (out == 2) {
+                            ended = true;
+                        } else if (out == 0) {
+                            if (p_ev >= A.max_events) {
+                                ended = truncated = true;
+                            } else {
+                                const V3 p = fma3(t, d, o);
+                                ++p_ev;
+                                T.pos[at] = make_float4(p.x, p.y, p.z, 0.0f);
+                                T.dir[at] = make_float4(d.x, d.y, d.z, 0.0f);
+                                T.light[at] = 1.0f;
+                                if ((absorbed >> ((chain << lg) + (int)e0)) & 1ull) {
+                                    ended = true;
+                                } else {
+                                    const float4 r = T.turn[at];
+                                    d = turn(d, r.x, r.y, r.z, r.w);
+                                    o = p;
+                                    t = 0.0f;
+                                }
+                            }
+                        }
+                        ++e0;
+                    }
+                }
+                // as many flights for every path, none past the event limit
+                uint32_t room = (uint32_t)GL;
+                if (live && !ended) {
+                    room = (uint32_t)GL - e0;
+                    if (A.max_events - p_ev < room) room = A.max_events - p_ev;
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    const uint32_t v = (uint32_t)__shfl_xor((int)room, off);
+                    room = v < room ? v : room;
+                }
+                const bool run = live && !ended;
+                const uint32_t steps = ballot(run) != 0 ? uniform_u32(room) : 0u;
+                const V3 o_first = o;
+                {
+                    // a path that ended has its last collisions in the slots:
+                    // it follows along without writing
+                    const int at0 = slot0 + (int)e0;
+                    for (uint32_t j = 0; j < steps; ++j) {
+                        const int at = run ? at0 + (int)j : slot0;
+                        const float4 r = T.turn[at];
+                        const V3 p = fma3(T.flight[at], d, o);
+                        if (run) {
+                            T.pos[at] = make_float4(p.x, p.y, p.z, 0.0f);
+                            T.dir[at] = make_float4(d.x, d.y, d.z, 0.0f);
+                        }
+                        d = turn(d, r.x, r.y, r.z, r.w);
+                        o = p;
+                    }
+                }
+                wave_sync();
+                // each lane checks its flight
+                const bool followed = run && (uint32_t)mine >= e0 && (uint32_t)mine < e0 + steps;
+                const float4 dm = T.dir[slot0 + mine], pm = T.pos[slot0 + mine];
+                const V3 d_mine = v3(dm.x, dm.y, dm.z), p_mine = v3(pm.x, pm.y, pm.z);
+                int out = 0;
+                float t_mine = 0.0f;
+                V3 o_mine = o_first;
+                if (followed) {
+                    if ((uint32_t)mine > e0) {
+                        const float4 pp = T.pos[slot0 + mine - 1];
+                        o_mine = v3(pp.x, pp.y, pp.z);
+                    }
+                    out = fly(o_mine, d_mine, t_mine, l_mine, false);
+                    // it began outside the body by a rounding
+                    if (out == 0 && t_mine != l_mine) out = 3;
+                }
+                const uint64_t followed_m = ballot(followed) & my_bits;
+                const uint64_t left_m = ballot(followed && out != 0) & my_bits, abs_m = absorbed & followed_m;
+                // the first flight that left, the first collision that absorbed
+                const int f_left = left_m ? __builtin_ctzll(left_m) : 64, f_abs = abs_m ? __builtin_ctzll(abs_m) : 64;
+                const bool valid = followed && lane < f_left && lane <= f_abs;
+                const bool lit = valid || T.light[slot0 + mine] != 0.0f;
+                float light = 0.0f;
+                if constexpr (kWaveLight) {
+                    uint64_t mk[kMaxManyPrims / 64];
+                    G.light_mask(A, lit, p_mine, mk);
+                    if (lit) light = G.light_masked(A, p_mine, d_mine, mk);
+                } else {
+                    if (lit) light = G.light(A, p_mine, d_mine);
+                }
+                T.light[slot0 + mine] = light;
+                const uint64_t valid_m = ballot(valid) & my_bits;
+                wave_sync();
+                for (int e = 0; e < GL; ++e) Lp = __builtin_fmaf(A.albedo, T.light[slot0 + e], Lp);
+                c0 += e0 + (run ? steps : 0u);
+                if (run) {
+                    p_ev += (uint32_t)__popcll(valid_m);
+                    if (f_abs < f_left) {
+                        ended = true;
+                    } else if (f_left < 64) {
+                        // back to the flight that left
+                        const int at = slot0 + f_left - (chain << lg);
+                        c0 -= e0 + steps - (uint32_t)(f_left - (chain << lg)) - 1u;
+                        const float4 df = T.dir[at];
+                        d = v3(df.x, df.y, df.z);
+                        if ((uint32_t)(f_left - (chain << lg)) > e0) {
+                            const float4 pf = T.pos[at - 1];
+                            o = v3(pf.x, pf.y, pf.z);
+                        } else {
+                            o = o_first;
+                        }
+                    }
+                }
+                const int out_f = __shfl(out, f_left & 63);
+                const float t_f = __shfl(t_mine, f_left & 63);
+                if (run && !ended && f_left < 64) {
+                    if (out_f == 2) ended = true;
+                    redo = out_f == 3;
+                    c0 -= redo ? 1u : 0u;
+                    t = redo ? 0.0f : t_f;
+                }
+                if (live && ended) {
+                    if (truncated && leader) tot[T_TRUNC][home] += 1;
+                    const uint32_t unit = tot[U_UNIT][home];
+                    const int s_next = bank(home, leader);
+                    if (s_next >= 0) {
+                        const ColdArgs C = cold_args();
+                        begin_path(udiv_exact(unit, (uint32_t)C->n_chunks, C->inv_n_chunks), s_next);
+                        if (leader) tot[U_NEXT][home] = (uint32_t)(s_next + 1);
+                    } else {
+                        live = false;
+                    }
+                }
+                n_now = __popcll(ballot(live && leader));
+                wave_sync();
+            } while (2 * n_now > 64 / GL || (GL == 64 && n_now > 0));
+        }
+    };
+
     // Collisions, and for the learned method the decoder passes, repeat in a
     // loop of their own until a restart is due, so that the restart phase's
     // working set does not weigh on them (measured 5-6 % faster for plain
@@ -1151,6 +1400,12 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     for (;;) {
         if (restart_due) restart();
         if (ballot(state != S_DONE) == 0) break;
+        if constexpr (MODE == kModePlain) {
+            if (pool.dry && __popcll(ballot(state != S_DONE)) <= kTraceTogether) {
+                trace_together();
+                break;
+            }
+        }
         do {
             bool path_end = false, truncated = false;
             collide(path_end, truncated);
@@ -1180,7 +1435,10 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
 // (three waves) despite a few spilled registers.
 template <int MODE, int NP, bool GRID>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(const RenderArgs A) {
-    __shared__ RenderLds lds_all[kRenderWaves];
+    // decoder rows (learned steps) and paths traced together (plain tracing):
+    // an instance only allocates what it uses
+    __shared__ RenderLds lds_rows[kRenderWaves];
+    __shared__ TogetherLds lds_paths[kRenderWaves];
     __shared__ uint32_t lds_tot[kLaneWords][64 * kRenderWaves];
     // many primitives: the scene's n_prims x 8 floats in dynamic LDS, sized
     // at launch, so that the usual scenes (64 spheres: 2 KB) leave room for
@@ -1188,32 +1446,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     extern __shared__ float lds_dyn[];
     __shared__ float lds_none[8];
     float* lds_prims = NP == 0 ? lds_dyn : lds_none;
-    RenderLds& L = lds_all[threadIdx.x >> 6];
+    RenderLds& L = lds_rows[threadIdx.x >> 6];
+    TogetherLds& T = lds_paths[threadIdx.x >> 6];
     __shared__ BlockTotals totals;
-    // models that the check before this launch refused: nothing is traced
-    if (MODE == kModeStCvae && A.ticket[1] != 0) return;
+    // refused models: nothing is traced; a launch that traces plainly queues
+    // the plain kernel beside the sphere tracer's, and the other one returns
+    if (A.ticket[1] != 0 || (A.gated && (A.ticket[2] != 0) != (MODE == kModePlain))) return;
     totals.reset();
     if (NP == 0) {
         for (int q = threadIdx.x; q < A.n_prims * 8; q += blockDim.x) lds_prims[q] = A.prims[q];
         __syncthreads();
     }
-    if (MODE != kModePlain) {
-        // No point of the scene reaches tau_min (the deepest point of the
-        // deepest primitive, or the step cap, is too shallow), or the deepest
-        // possible step would bypass fewer than min_chain collisions (the
-        // launch's cost rule): every collision is a plain one, so the plain
-        // loop runs -- the same paths and draws, without the learned step's
-        // checks and register pressure.
-        typename GeoSel<NP, GRID>::type G;
-        G.init(A, lds_prims);
-        const float t_max = A.sigma_t * __builtin_fminf(G.max_radius(), A.st_max * A.inv_sigma_t);
-        const bool pays = !(A.min_chain > 0.0f) || 0.5f * t_max * t_max * (1.0f - A.g) >= A.min_chain;
-        if (!(t_max >= A.tau_min) || !pays) {
-            render_loop<kModePlain, NP, GRID>(A, L, lds_prims, lds_tot, totals);
-            return;
-        }
-    }
-    render_loop<MODE, NP, GRID>(A, L, lds_prims, lds_tot, totals);
+    render_loop<MODE, NP, GRID>(A, L, lds_prims, lds_tot, totals, T);
 }
 
 // Per-pixel fixed-order reduction of the unit partials, added to the image
@@ -1269,28 +1513,47 @@ __global__ void render_reduce_kernel(int64_t npix, int n_chunks, int spp, const 
     }
 }
 
-// ticket[0]: the counter past the tickets that the waves begin with;
-// ticket[1]: whether the models are refused.
-__global__ void render_check_models(const RenderArgs A, uint64_t first) {
-    if (threadIdx.x != 0) return;
-    const int want_in[3] = {2, 3, 7}, want_out[3] = {1, 3, 6};
-    int ok = 1;
-    for (int m = 0; m < 3; ++m) {
-        const PackedModel* pm = A.pm[m];
-        ok &= pm->magic == (int32_t)kPackedMagic && pm->model == m && pm->latent >= 1 && pm->latent <= 8 &&
-              pm->latent + pm->p_in <= 16 && pm->p_in == want_in[m] && pm->p_out == want_out[m] &&
-              (pm->precision == MS_PREC_BF16 || pm->precision == MS_PREC_FP8) && pm->n_linear >= 2 &&
-              pm->n_linear <= kMaxLayers && pm->blocks == 1 && pm->width <= 16;
+// Does a sphere-tracing launch of an analytic scene trace plainly?  Where no
+// point of the scene reaches tau_min (the deepest point of the deepest
+// primitive -- a sphere's centre at depth r, a box's at its smallest half size,
+// in the rounding of union_radius -- or the step cap is too shallow), or the
+// deepest possible step would bypass fewer than min_chain collisions (the
+// launch's cost rule), every collision is a plain one: the plain kernel has the
+// same paths and draws, without the learned step's checks and registers.
+__host__ __device__ __forceinline__ bool traces_plainly(const RenderArgs& A, float deepest) {
+    const float t_max = A.sigma_t * (deepest < A.r_cap ? deepest : A.r_cap);
+    const bool pays = !(A.min_chain > 0.0f) || 0.5f * t_max * t_max * (1.0f - A.g) >= A.min_chain;
+    return !(t_max >= A.tau_min) || !pays;
+}
+__device__ __forceinline__ float deepest_radius(const RenderArgs& A) {
+    float m = 0.0f;
+    for (int i = 0; i < A.n_prims; ++i) {
+        const float* p = A.prims + 8 * i;
+        m = __builtin_fmaxf(m, p[0] == 0.0f ? p[4] : __builtin_fminf(p[4], __builtin_fminf(p[5], p[6])));
     }
-    A.ticket[0] = first;
-    A.ticket[1] = ok ? 0ull : 1ull;
+    return union_radius(-m);
 }
 
-__global__ void render_start_kernel(unsigned long long* ticket, uint64_t first) {
-    if (threadIdx.x == 0) {
-        ticket[0] = first;
-        ticket[1] = 0ull;
+// Before every launch.  ticket[1]: whether the models are refused; ticket[2]:
+// with two kernels queued, whether the plain one runs; ticket[0]: the counter
+// past the tickets that the running kernel's waves begin with.
+__global__ void render_start_kernel(const RenderArgs A, int learned, uint64_t first, uint64_t first_plain) {
+    if (threadIdx.x != 0) return;
+    int ok = 1;
+    if (learned) {
+        const int want_in[3] = {2, 3, 7}, want_out[3] = {1, 3, 6};
+        for (int m = 0; m < 3; ++m) {
+            const PackedModel* pm = A.pm[m];
+            ok &= pm->magic == (int32_t)kPackedMagic && pm->model == m && pm->latent >= 1 && pm->latent <= 8 &&
+                  pm->latent + pm->p_in <= 16 && pm->p_in == want_in[m] && pm->p_out == want_out[m] &&
+                  (pm->precision == MS_PREC_BF16 || pm->precision == MS_PREC_FP8) && pm->n_linear >= 2 &&
+                  pm->n_linear <= kMaxLayers && pm->blocks == 1 && pm->width <= 16;
+        }
     }
+    const bool plain = A.gated && traces_plainly(A, deepest_radius(A));
+    A.ticket[0] = plain ? first_plain : first;
+    A.ticket[1] = ok ? 0ull : 1ull;
+    A.ticket[2] = plain ? 1ull : 0ull;
 }
 
 // Conservative FP16 distance grid (the voxel-grid distance pre-process of
@@ -1469,7 +1732,8 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     A.sampler = desc->sampler;
     for (int m = 0; m < 3; ++m) A.pm[m] = reinterpret_cast<const PackedModel*>(desc->packed[m]);
     A.tau_min = desc->tau_min;
-    A.st_max = desc->st_max;
+    A.r_cap = desc->st_max * A.inv_sigma_t;
+    A.hg = hg_const(medium->g);
     A.min_chain = desc->min_chain;
     A.spp = desc->spp;
     A.chunk = desc->chunk > 0 ? (desc->chunk < desc->spp ? desc->chunk : desc->spp) : default_chunk(A.npix, desc->spp);
@@ -1488,33 +1752,56 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     A.flags = desc->flags;
     char* ws = reinterpret_cast<char*>(workspace_dev);
     A.ticket = reinterpret_cast<unsigned long long*>(ws);
-    unsigned long long* flag = A.ticket + 1;
     A.part = reinterpret_cast<UnitRecord*>(ws + 256);
     A.counters = reinterpret_cast<unsigned long long*>(out->counters);
 
     hipStream_t hs = (hipStream_t)stream;
     const int bpc = desc->blocks_per_cu ? desc->blocks_per_cu : 4;
-    int64_t blocks = (int64_t)cus * bpc;
-    const int64_t need_blocks = (A.n_units + 255) / 256;
-    if (blocks > need_blocks) blocks = need_blocks;
-    const uint64_t first = (uint64_t)blocks * kRenderWaves * kTickets;
-    if (learned) hipLaunchKernelGGL(render_check_models, dim3(1), dim3(64), 0, hs, A, first);
-    else hipLaunchKernelGGL(render_start_kernel, dim3(1), dim3(64), 0, hs, A.ticket, first);
-    MS_LAUNCHED();
-    const int mode = desc->method == MS_METHOD_PLAIN_NEE ? kModePlain
-                     : (desc->sampler == MS_SAMPLER_EXACT_WALK ? kModeStExact : kModeStCvae);
-    const dim3 grid((unsigned)blocks), block(64 * kRenderWaves);
+    // Few work units are spread over all waves where the last paths of a wave
+    // are traced together: the fewer it has, the sooner.
+    struct Shape {
+        int lanes;
+        int64_t blocks;
+        uint64_t first() const { return (uint64_t)blocks * kRenderWaves * lanes; }
+    };
+    auto shape = [&](bool spread) {
+        const int64_t most = (int64_t)cus * bpc;
+        Shape h{spread ? 8 : 64, 0};
+        while (h.lanes < 64 && A.n_units > h.lanes * most * kRenderWaves) h.lanes *= 2;
+        h.blocks = (A.n_units + kRenderWaves * h.lanes - 1) / (kRenderWaves * h.lanes);
+        if (h.blocks > most) h.blocks = most;
+        return h;
+    };
+    const Shape plain = shape(true), st_shape = shape(false);
+    int mode = desc->method == MS_METHOD_PLAIN_NEE ? kModePlain
+               : (desc->sampler == MS_SAMPLER_EXACT_WALK ? kModeStExact : kModeStCvae);
     const bool grid_r = A.grid != nullptr;
-    if (mesh) launch_render<kGeoMesh, true>(mode, grid, block, hs, A);
-    else if (A.n_prims <= 1) grid_r ? launch_render<1, true>(mode, grid, block, hs, A) : launch_render<1, false>(mode, grid, block, hs, A);
-    else if (A.n_prims == 2) grid_r ? launch_render<2, true>(mode, grid, block, hs, A) : launch_render<2, false>(mode, grid, block, hs, A);
-    else if (A.n_prims <= 4) grid_r ? launch_render<4, true>(mode, grid, block, hs, A) : launch_render<4, false>(mode, grid, block, hs, A);
-    else grid_r ? launch_render<0, true>(mode, grid, block, hs, A) : launch_render<0, false>(mode, grid, block, hs, A);
+    // the primitives are on the device: where their depth counts, so is the
+    // choice, between two queued kernels
+    A.gated = mode != kModePlain && !mesh && !grid_r && A.n_prims <= 4;
+    if (mode != kModePlain && !A.gated && traces_plainly(A, INFINITY)) mode = kModePlain;
+    const Shape own = mode == kModePlain ? plain : st_shape;
+    hipLaunchKernelGGL(render_start_kernel, dim3(1), dim3(64), 0, hs, A, learned ? 1 : 0, own.first(), plain.first());
     MS_LAUNCHED();
+    auto launch = [&](int m, const Shape& h) {
+        const dim3 grid((unsigned)h.blocks), block(64 * kRenderWaves);
+        A.lanes = h.lanes;
+        if (mesh) launch_render<kGeoMesh, true>(m, grid, block, hs, A);
+        else if (A.n_prims <= 1) grid_r ? launch_render<1, true>(m, grid, block, hs, A) : launch_render<1, false>(m, grid, block, hs, A);
+        else if (A.n_prims == 2) grid_r ? launch_render<2, true>(m, grid, block, hs, A) : launch_render<2, false>(m, grid, block, hs, A);
+        else if (A.n_prims <= 4) grid_r ? launch_render<4, true>(m, grid, block, hs, A) : launch_render<4, false>(m, grid, block, hs, A);
+        else grid_r ? launch_render<0, true>(m, grid, block, hs, A) : launch_render<0, false>(m, grid, block, hs, A);
+    };
+    launch(mode, own);
+    MS_LAUNCHED();
+    if (A.gated) {
+        launch(kModePlain, plain);
+        MS_LAUNCHED();
+    }
     int64_t rb = (A.npix + 3) / 4;  // four pixels (waves) per block
     if (rb > cus * 16) rb = cus * 16;
     hipLaunchKernelGGL(render_reduce_kernel, dim3((unsigned)rb), dim3(256), 0, hs, A.npix, A.n_chunks, A.spp, A.part,
-                       out->sum, out->comp, out->sumsq, out->events, out->steps, flag, A.counters);
+                       out->sum, out->comp, out->sumsq, out->events, out->steps, A.ticket + 1, A.counters);
     MS_LAUNCHED();
     clear_error();
     return MS_OK;

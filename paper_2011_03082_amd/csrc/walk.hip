@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
     __shared__ BlockTotals totals;
     totals.reset();
     TicketPool pool;
-    pool.reset((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6), a.width);
+    pool.reset((uint64_t)blockIdx.x * 4 + uniform_u32(threadIdx.x >> 6), (uint64_t)gridDim.x * 4, a.width, a.n);
     // lane state: walking, ended (record not yet written), idle, done
     bool active = false, ended = false, done = lane_id() >= a.width;
     bool absorbed = false, truncated = false;
@@ -156,6 +156,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
     V3 x = v3(0, 0, 0), d = v3(0, 0, 1), xk = v3(0, 0, 0), wk = v3(0, 0, 1);
     uint32_t nev = 0, c0 = 0, k = 1;
     float st = a.sigma_t, inv_st = 1.0f / a.sigma_t, g = a.g, phi = a.albedo, inv_phi = 1.0f, resv = 0.0f;
+    Hg hg = hg_const(a.g);
     const float r = MODE == MS_WALK_ANALOG ? a.radius : 1.0f;
     const float r2 = MODE == MS_WALK_ANALOG ? a.r2 : 1.0f;
     uint64_t n_events = 0, n_abs = 0, n_trunc = 0, n_max = 0;
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
             st = fromf(st);
             inv_st = fromf(inv_st);
             g = fromf(g);
+            if (MODE == MS_WALK_TRAINING) hg = hg_const(g);
             phi = fromf(phi);
             inv_phi = fromf(inv_phi);
             resv = fromf(resv);
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                 const uint32_t steps = left < (uint32_t)G ? left : (uint32_t)G;
                 const uint32_t mine = (uint32_t)(lane & (G - 1));
                 const uint4 w = rng.block(c0 + mine);
-                const HgSample h = hg_sample(g, u01(w.y));
+                const HgSample h = hg_sample(hg, u01(w.y));
                 const float az = u01(w.z);
                 float l = -flight_ln(u01(w.x)) * inv_st, u = 0.0f;
                 if (MODE == MS_WALK_ANALOG) {
@@ -382,6 +384,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                     if (MODE == MS_WALK_TRAINING) {
                         training_params(a, id, st, g, phi);
                         inv_st = 1.0f / st;
+                        hg = hg_const(g);
                         // finite, so that the reservoir's first step gives 1
                         inv_phi = __builtin_fminf(1.0f / phi, 0x1.fffffep127f);
                     }
@@ -397,12 +400,8 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                     done = true;
                 }
             }
-            // with fewer than 64 lanes there is a wave for every `width`
-            // photons, and each takes its own once
-            if (a.width < 64) done = !active;
-            const uint64_t dmask = ballot(done);
-            if (dmask == ~0ull) break;
-            if (dmask != 0 && __popcll(ballot(active)) <= kWalkTogether) {
+            if (ballot(!done) == 0) break;
+            if (pool.dry && __popcll(ballot(!done)) <= kWalkTogether) {
                 walk_together();
                 break;
             }
@@ -434,7 +433,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                 }
             }
             if (!stop) {
-                const HgSample h = hg_sample(g, u01(w.y));
+                const HgSample h = hg_sample(hg, u01(w.y));
                 d = scatter(d, h.mu, h.sin_t, u01(w.z));
                 const float l = -flight_ln(u01(w.x)) * inv_st;
                 const V3 xn = fma3(l, d, x);

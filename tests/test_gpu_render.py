@@ -574,3 +574,41 @@ def test_rgb_media_channel_by_channel(msst, oracle):
         print(f"channel {c}: diverged {frac:.2e}, mean {o['sum'].mean():.4e}")
         assert frac < 3.5e-3
 
+
+def together_scene(msst, name, w, h):
+    """Renderers of every geometry: one to four primitives, many with and
+    without a grid, a mesh."""
+    c4, cam, light = W.scene_c4(), W.camera_c4(w, h), W.light_c4()
+    extra = np.array([W.prim_sphere((-0.61, 0.53, 0.31), 0.47), W.prim_box((0.0, -1.0, 0.0), (0.3, 0.5, 0.3))], np.float32)
+    if name == "sphere":
+        return msst.Renderer(W.scene_sphere(0.7), cam, light)
+    if name in ("two", "three", "four"):
+        return msst.Renderer(np.concatenate([c4, extra])[: {"two": 2, "three": 3, "four": 4}[name]], cam, light)
+    if name == "many":
+        return msst.Renderer(W.scene_c5(4, 20), W.camera_c5(w, h), W.light_c5())
+    if name == "many_grid":
+        prims = W.scene_c5(3, 40)
+        return msst.Renderer(prims, W.camera_c5(w, h), W.light_c5(), grid=msst.build_sdf_grid(prims, 96))
+    lo, hi, tris = (-1.2,) * 3, (1.2,) * 3, W.mesh_blob(2, 3)
+    grid = msst.build_sdf_grid(None, 48, lo, hi, tris=tris)
+    return msst.Renderer(None, W.camera_mesh(w, h), light, grid=grid, grid_lo=lo, grid_hi=hi, tris=tris)
+
+
+@pytest.mark.parametrize("name", ["sphere", "two", "three", "four", "many", "many_grid", "mesh"])
+@pytest.mark.parametrize("sigma_t,albedo,kw", [(20.0, 0.995, dict(spp=3, chunk=2)), (60.0, 0.9999, dict(spp=1)),
+                                               (30.0, 1.0, dict(spp=2, max_events=9)), (8.0, 0.6, dict(spp=5, max_events=1))])
+def test_paths_traced_together_are_the_same(msst, name, sigma_t, albedo, kw):
+    """A launch of few work units spreads them over all waves, which trace
+    their paths together (8 or more lanes per path); one block per CU fills
+    its waves and traces a path per lane until its last ones.  Images, counts
+    and counters are the same bit for bit: flights that start at the camera,
+    at the boundary and at a collision, absorption, event limits, several
+    samples per unit."""
+    announce(f"render together {name} sigma_t={sigma_t} {kw}")
+    r = together_scene(msst, name, 300, 240)
+    med = dict(sigma_t=sigma_t, g=0.8, albedo=albedo)
+    wide = r.render(med, method=PLAIN, seed=5, blocks_per_cu=1, **dict(dict(chunk=1), **kw))
+    spread = r.render(med, method=PLAIN, seed=5, blocks_per_cu=64, **dict(dict(chunk=1), **kw))
+    for k in wide:
+        assert torch.equal(wide[k], spread[k]), (k, int((wide[k] != spread[k]).sum()))
+    assert int(wide["counters"][1]) > 1000
