@@ -388,12 +388,18 @@ struct TrainArgs {
     double* loss_partial; // [blocks][2]
 };
 
-// Per-wave LDS: inputs of the 2 NL layers and two work buffers, each 16 T
-// feature rows (T stacked 16 x 16 tiles) of 16 samples.
-template <int T>
+// Per-wave LDS: what passes between lanes, 16 T feature rows (T stacked 16 x 16
+// tiles) of 16 samples each.  Layer inputs and their gradients are held as the
+// bfloat16 values that the products take.
+template <int NL, int T>
 struct WaveLds {
-    float act[2 * kMaxNL][kTile * kTile * T];
-    float work[2][kTile * kTile * T];
+    __bf16 act[2 * NL][kTile * T][kTile];   // inputs of the 2 NL layers
+    __bf16 dpre[2 * NL][kTile * T][kTile];  // gradients of their linear outputs
+    float enc[kTile * T][kTile];            // encoder output: mean, log variance
+    float dec[kTile * T][kTile];            // decoder output
+    float y[kTile][kTile];                  // target
+    float eps[kTile][kTile], dz[kTile][kTile];
+    float kl[kTile][kTile], nll[kTile][kTile];  // a sample's loss, term by term
 };
 
 // Weight fragments of block (o, k) of a layer with row stride 16 T: the A
@@ -414,24 +420,34 @@ __device__ __forceinline__ bf16x4 wt_frag(const float* layer, int o, int k) {
 template <int T>
 __device__ __forceinline__ f32x4 bias_d(const float* layer, int o) {
     constexpr int S = kTile * T;
-    const float* b = layer + S * S + kTile * o + frag_k0();
-    return f32x4{b[0], b[1], b[2], b[3]};
+    return *reinterpret_cast<const f32x4*>(layer + S * S + kTile * o + frag_k0());
 }
 
-// Forward of one net (NL layers starting at FIRST) from act[FIRST]; the last
-// layer's output blocks go to `out`.  Hidden units at or beyond `width` do
-// not exist: their activations are forced to 0, so their (zero-initialised)
-// weights and biases receive zero gradients.
+// A tile of 16 features by 16 samples in LDS as bfloat16: stored from the D
+// layout (this lane's four rows of its column), and read transposed (row
+// frag_row(), four consecutive samples: an operand of dPre X^T).
+__device__ __forceinline__ void tile_put(__bf16 (*t)[kTile], bf16x4 v) {
+    const int c = frag_row(), k0 = frag_k0();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[k0 + q][c] = v[q];
+}
+__device__ __forceinline__ bf16x4 tile_get_t(const __bf16 (*t)[kTile]) {
+    return *reinterpret_cast<const bf16x4*>(&t[frag_row()][frag_k0()]);
+}
+
+// Forward of one net (NL layers starting at FIRST) from its input x, the B
+// operand of this lane (which act[FIRST] holds for the backward pass); the
+// last layer's output blocks go to `out`.  The D layout of a layer's output is
+// the next one's B operand, so the chain stays in registers.  Hidden units at
+// or beyond `width` do not exist: their activations are forced to 0, so their
+// (zero-initialised) weights and biases receive zero gradients.
 template <int FIRST, int NL, int T>
-__device__ __forceinline__ void net_forward(const bf16x4 (*wf)[T][T], const f32x4 (*bs)[T], WaveLds<T>& L,
-                                            f32x4 (*pre)[T], int width, f32x4* out) {
+__device__ __forceinline__ void net_forward(const bf16x4 (*wf)[T][T], const f32x4 (*bs)[T], WaveLds<NL, T>& L,
+                                            f32x4 (*pre)[T], int width, bf16x4* x, f32x4* out) {
     const int k0 = frag_k0();
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
         const int layer = FIRST + j;
-        bf16x4 x[T];
-#pragma unroll
-        for (int k = 0; k < T; ++k) x[k] = to_bf16x4(tile_load_d(L.act[layer] + kTile * kTile * k));
 #pragma unroll
         for (int o = 0; o < T; ++o) {
             f32x4 acc = bs[layer][o];
@@ -445,48 +461,36 @@ __device__ __forceinline__ void net_forward(const bf16x4 (*wf)[T][T], const f32x
             for (int o = 0; o < T; ++o) {
                 f32x4 a;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    a[q] = kTile * o + k0 + q < width ? bf16_round(softplus(pre[layer][o][q])) : 0.0f;
-                tile_store_d(L.act[layer + 1] + kTile * kTile * o, a);
+                for (int q = 0; q < 4; ++q) a[q] = kTile * o + k0 + q < width ? softplus(pre[layer][o][q]) : 0.0f;
+                x[o] = to_bf16x4(a);
+                tile_put(L.act[layer + 1] + kTile * o, x[o]);
             }
-            wave_sync();
         }
     }
 }
 
-// Backward of one net given d loss / d (last linear output) in D layout.
-// Accumulates dW (D layout: row = output unit, column = input unit) and db,
+// Backward of one net given d loss / d (last linear output) in D layout, which
+// is also the B operand of dX = W^T dPre: the chain stays in registers.  Adds
+// db, leaves the rounded dPre of every layer in LDS for the weight gradients,
 // and writes d loss / d (input of the first layer) in D layout to dx.
 template <int FIRST, int NL, int T>
-__device__ __forceinline__ void net_backward(const bf16x4 (*wt)[T][T], WaveLds<T>& L, const f32x4 (*pre)[T],
-                                             f32x4* dpre, f32x4 (*dw)[T][T], f32x4 (*db)[T], f32x4* dx) {
+__device__ __forceinline__ void net_backward(const bf16x4 (*wt)[T][T], WaveLds<NL, T>& L, const f32x4 (*pre)[T],
+                                             f32x4* dpre, f32x4 (*db)[T], f32x4* dx) {
 #pragma unroll
     for (int j = NL - 1; j >= 0; --j) {
         const int layer = FIRST + j;
+        bf16x4 d[T];
 #pragma unroll
         for (int o = 0; o < T; ++o) {
             db[layer][o] += dpre[o];
-            // dW += dPre X^T: both operands read transposed from LDS
-            tile_store_d(L.work[0] + kTile * kTile * o, f32x4{bf16_round(dpre[o][0]), bf16_round(dpre[o][1]),
-                                                               bf16_round(dpre[o][2]), bf16_round(dpre[o][3])});
+            d[o] = to_bf16x4(dpre[o]);
+            tile_put(L.dpre[layer] + kTile * o, d[o]);
         }
-        wave_sync();
-#pragma unroll
-        for (int o = 0; o < T; ++o) {
-            const bf16x4 a = to_bf16x4(tile_load_t(L.work[0] + kTile * kTile * o));
-#pragma unroll
-            for (int k = 0; k < T; ++k) {
-                const bf16x4 b = to_bf16x4(tile_load_t(L.act[layer] + kTile * kTile * k));
-                dw[layer][o][k] = mfma_bf16(a, b, dw[layer][o][k]);
-            }
-        }
-        wave_sync();
-        // dX = W^T dPre
 #pragma unroll
         for (int k = 0; k < T; ++k) {
             f32x4 acc = f32x4{0, 0, 0, 0};
 #pragma unroll
-            for (int o = 0; o < T; ++o) acc = mfma_bf16(wt[layer][o][k], to_bf16x4(dpre[o]), acc);
+            for (int o = 0; o < T; ++o) acc = mfma_bf16(wt[layer][o][k], d[o], acc);
             dx[k] = acc;
         }
         if (j > 0) {
@@ -499,23 +503,67 @@ __device__ __forceinline__ void net_backward(const bf16x4 (*wt)[T][T], WaveLds<T
     }
 }
 
+// Sum over the 16 lanes of a row (the same in every lane): each step adds the
+// value of a lane whose partial sum covers the other half.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    return dpp_add<0x140>(v);  // row_mirror
+}
+
+// A step of 4096 samples is one tile per wave, one wave per SIMD: bound by the
+// latency of one tile's chain of dependent steps, so all 64 lanes take part in
+// each (a lane holds 4 T of the 16 T rows of its sample), the layers chain in
+// registers, rows are gathered ahead of the weights, and the weight gradients'
+// transposed products wait for the end of the tile.
 template <int NL, int T>
 __global__ __launch_bounds__(256) void cvae_train_kernel(const TrainArgs a) {
-    constexpr int TT = kTile * kTile * T;  // floats of one activation buffer
-    constexpr int S = kTile * T;           // row stride of a layer's weights
-    constexpr int LF = S * S + S;          // floats per layer
-    constexpr int kLat = 8 * T;            // latent sizes up to 8 T (2 L <= 16 T)
-    __shared__ WaveLds<T> lds_all[kTrainWaves];
-    const int wave = threadIdx.x >> 6;
-    WaveLds<T>& L = lds_all[wave];
+    constexpr int S = kTile * T;   // row stride of a layer's weights
+    constexpr int LF = S * S + S;  // floats per layer
+    constexpr int kParams = 2 * NL * LF;
+    typedef WaveLds<NL, T> Lds;
+    __shared__ __align__(16) Lds lds_all[kTrainWaves];
+    const int wave = uniform_u32(threadIdx.x >> 6);
+    Lds& L = lds_all[wave];
     const Shape s = a.s;
-    constexpr int nl = NL;
     const int P = s.p_out, Lt = s.latent, C = s.p_in;
-    const int lane = lane_id();
+    const int lane = lane_id(), c = frag_row(), k0 = frag_k0();
     const float inv_b = 1.0f / (float)a.batch;
 
+    // this lane's rows k0 .. k0 + 3 of each block of (target, cond), sample
+    // column c of a tile
+    auto gather = [&](int tile, f32x4* x) __attribute__((always_inline)) {
+        const int b = tile * kTile + c;
+        int64_t row = b;
+        if (a.sample_rows) {
+            const Rng rb = make_rng(a.seed, MS_TAG_CVAE_BATCH, (uint64_t)b);
+            row = (int64_t)(((uint64_t)rb.block((uint32_t)a.step).x * (uint64_t)a.n_rows) >> 32);
+        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = kTile * k + k0 + q;
+                float v = 0.0f;
+                if (r < P) v = a.target[row * P + r];
+                else if (r < P + C) v = a.cond[row * C + (r - P)];
+                x[k][q] = v;
+            }
+        }
+    };
+    const int n_tiles = a.batch / kTile;
+    const int wave_global = blockIdx.x * kTrainWaves + wave;
+    const int n_waves = gridDim.x * kTrainWaves;
+    f32x4 x_next[T];
+    if (wave_global < n_tiles) gather(wave_global, x_next);
+
     // all layers' weight fragments (both orientations) and biases of this
-    // lane, loaded once: the tile loop is a chain of dependent steps
+    // lane, loaded once
     bf16x4 wf[2 * NL][T][T], wt[2 * NL][T][T];
     f32x4 bs[2 * NL][T];
 #pragma unroll
@@ -543,170 +591,178 @@ __global__ __launch_bounds__(256) void cvae_train_kernel(const TrainArgs a) {
     }
     double kl_acc = 0.0, nll_acc = 0.0;
 
-    const int n_tiles = a.batch / kTile;
-    const int wave_global = blockIdx.x * kTrainWaves + wave;
-    const int n_waves = gridDim.x * kTrainWaves;
     for (int tile = wave_global; tile < n_tiles; tile += n_waves) {
-        const int b = tile * kTile + (lane & 15);  // sample of this lane's column
-        // zero the two input buffers, then gather (target, cond) rows
-        for (int q = lane; q < TT; q += 64) {
-            L.act[0][q] = 0.0f;
-            L.act[nl][q] = 0.0f;
+        // noise of latents k0 .. k0 + 3 (Philox block k0 / 4)
+        float eps[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k0 < Lt)
+            normals4(make_rng(a.seed, MS_TAG_CVAE_REPARAM, a.id_offset + (uint64_t)(tile * kTile + c)),
+                     (uint32_t)(4 * a.step + (k0 >> 2)), eps);
+        bf16x4 x[T];
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            x[k] = to_bf16x4(x_next[k]);
+            tile_put(L.act[0] + kTile * k, x[k]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (kTile * k + k0 + q < P) L.y[(kTile * k + k0 + q) & 15][c] = x_next[k][q];
         }
-        wave_sync();
-        float mu_z[kLat], lv_z[kLat], lvr_z[kLat], eps[kLat];
-        if (lane < 16) {
-            int64_t row = b;
-            if (a.sample_rows) {
-                const Rng rb = make_rng(a.seed, MS_TAG_CVAE_BATCH, (uint64_t)b);
-                row = (int64_t)(((uint64_t)rb.block((uint32_t)a.step).x * (uint64_t)a.n_rows) >> 32);
-            }
-            for (int k = 0; k < P; ++k) L.act[0][k * kTile + lane] = bf16_round(a.target[row * P + k]);
-            for (int k = 0; k < C; ++k) {
-                const float cv = bf16_round(a.cond[row * C + k]);
-                L.act[0][(P + k) * kTile + lane] = cv;
-                L.act[nl][(Lt + k) * kTile + lane] = cv;
-            }
-        }
-        wave_sync();
+        if (tile + n_waves < n_tiles) gather(tile + n_waves, x_next);
         // encoder
-        f32x4 oe[T];
-        net_forward<0, NL, T>(wf, bs, L, pre, s.width, oe);
+        f32x4 out[T];
+        net_forward<0, NL, T>(wf, bs, L, pre, s.width, x, out);
 #pragma unroll
-        for (int o = 0; o < T; ++o) tile_store_d(L.work[0] + kTile * kTile * o, oe[o]);
+        for (int o = 0; o < T; ++o) tile_store_d(&L.enc[kTile * o][0], out[o]);
         wave_sync();
-        if (lane < 16) {
-            const Rng rr = make_rng(a.seed, MS_TAG_CVAE_REPARAM, a.id_offset + (uint64_t)b);
-            for (int j = 0; 4 * j < Lt; ++j) normals4(rr, (uint32_t)(4 * a.step + j), eps + 4 * j);
-            float kl = 0.0f;
-            for (int i = 0; i < Lt; ++i) {
-                mu_z[i] = L.work[0][i * kTile + lane];
-                lvr_z[i] = L.work[0][(Lt + i) * kTile + lane];
-                lv_z[i] = clamp_lv(lvr_z[i]);
-                const float z = __builtin_fmaf(fast_exp(0.5f * lv_z[i]), eps[i], mu_z[i]);
-                L.act[nl][i * kTile + lane] = bf16_round(z);
-                kl += 0.5f * (mu_z[i] * mu_z[i] + fast_exp(lv_z[i]) - lv_z[i] - 1.0f);
+        // z after the reparametrisation, then the condition
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = kTile * k + k0 + q;
+                __bf16 v = (__bf16)0.0f;
+                if (r < Lt) {
+                    const float mu = L.enc[r][c], lv = clamp_lv(L.enc[Lt + r][c]);
+                    v = (__bf16)__builtin_fmaf(fast_exp(0.5f * lv), eps[q], mu);
+                    L.kl[r & 15][c] = __builtin_fmaf(mu, mu, fast_exp(lv)) - lv - 1.0f;
+                    L.eps[r & 15][c] = eps[q];
+                } else if (r < Lt + C) {
+                    v = L.act[0][P + r - Lt][c];
+                }
+                x[k][q] = v;
             }
-            kl_acc += (double)kl;
+            tile_put(L.act[NL] + kTile * k, x[k]);
         }
-        wave_sync();
         // decoder
-        f32x4 od[T];
-        net_forward<NL, NL, T>(wf, bs, L, pre, s.width, od);
+        net_forward<NL, NL, T>(wf, bs, L, pre, s.width, x, out);
 #pragma unroll
-        for (int o = 0; o < T; ++o) tile_store_d(L.work[0] + kTile * kTile * o, od[o]);
-        for (int q = lane; q < TT; q += 64) L.work[1][q] = 0.0f;
-        wave_sync();
-        if (lane < 16) {
-            int64_t row = b;
-            if (a.sample_rows) {
-                const Rng rb = make_rng(a.seed, MS_TAG_CVAE_BATCH, (uint64_t)b);
-                row = (int64_t)(((uint64_t)rb.block((uint32_t)a.step).x * (uint64_t)a.n_rows) >> 32);
-            }
-            float nll = 0.0f;
-            for (int k = 0; k < P; ++k) {
-                const float mu = L.work[0][k * kTile + lane];
-                const float lvr = L.work[0][(P + k) * kTile + lane];
-                const float lv = clamp_lv(lvr);
-                const float y = a.target[row * P + k];
-                const float r = y - mu, iv = fast_exp(-lv);
-                nll += 0.5f * (kLog2Pi + lv + r * r * iv);
-                L.work[1][k * kTile + lane] = -r * iv * inv_b;
-                L.work[1][(P + k) * kTile + lane] = 0.5f * (1.0f - r * r * iv) * clamp_mask(lvr) * inv_b;
-            }
-            nll_acc += (double)nll;
-        }
+        for (int o = 0; o < T; ++o) tile_store_d(&L.dec[kTile * o][0], out[o]);
         wave_sync();
         f32x4 dcur[T], dzc[T];
 #pragma unroll
-        for (int o = 0; o < T; ++o) dcur[o] = tile_load_d(L.work[1] + kTile * kTile * o);
-        net_backward<NL, NL, T>(wt, L, pre, dcur, dw, db, dzc);
+        for (int o = 0; o < T; ++o) {
 #pragma unroll
-        for (int o = 0; o < T; ++o) tile_store_d(L.work[0] + kTile * kTile * o, dzc[o]);
-        for (int q = lane; q < TT; q += 64) L.work[1][q] = 0.0f;
-        wave_sync();
-        if (lane < 16) {
-            for (int i = 0; i < Lt; ++i) {
-                const float dz = L.work[0][i * kTile + lane];
-                const float sd = fast_exp(0.5f * lv_z[i]);
-                L.work[1][i * kTile + lane] = dz + a.kl_weight * mu_z[i] * inv_b;
-                L.work[1][(Lt + i) * kTile + lane] =
-                    (0.5f * dz * eps[i] * sd + a.kl_weight * 0.5f * (fast_exp(lv_z[i]) - 1.0f) * inv_b) *
-                    clamp_mask(lvr_z[i]);
+            for (int q = 0; q < 4; ++q) {
+                const int r = kTile * o + k0 + q, k = r < P ? r : r - P;
+                float v = 0.0f;
+                if (r < 2 * P) {
+                    const float mu = L.dec[k][c], lvr = L.dec[P + k][c], lv = clamp_lv(lvr);
+                    const float e = L.y[k & 15][c] - mu, iv = fast_exp(-lv);
+                    if (r < P) {
+                        L.nll[k & 15][c] = __builtin_fmaf(e * e, iv, kLog2Pi + lv);
+                        v = -e * iv * inv_b;
+                    } else {
+                        v = 0.5f * __builtin_fmaf(-(e * e), iv, 1.0f) * clamp_mask(lvr) * inv_b;
+                    }
+                }
+                dcur[o][q] = v;
             }
         }
+        net_backward<NL, NL, T>(wt, L, pre, dcur, db, dzc);
+        tile_store_d(&L.dz[0][0], dzc[0]);
         wave_sync();
 #pragma unroll
-        for (int o = 0; o < T; ++o) dcur[o] = tile_load_d(L.work[1] + kTile * kTile * o);
-        net_backward<0, NL, T>(wt, L, pre, dcur, dw, db, dzc);
+        for (int o = 0; o < T; ++o) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = kTile * o + k0 + q, i = r < Lt ? r : r - Lt;
+                float v = 0.0f;
+                if (r < Lt) {
+                    v = __builtin_fmaf(a.kl_weight * L.enc[r][c], inv_b, L.dz[r & 15][c]);
+                } else if (r < 2 * Lt) {
+                    const float lvr = L.enc[r][c], lv = clamp_lv(lvr), sd = fast_exp(0.5f * lv);
+                    const float kl = a.kl_weight * 0.5f * (fast_exp(lv) - 1.0f) * inv_b;
+                    v = __builtin_fmaf(0.5f * L.dz[i & 15][c] * L.eps[i & 15][c], sd, kl) * clamp_mask(lvr);
+                }
+                dcur[o][q] = v;
+            }
+        }
+        net_backward<0, NL, T>(wt, L, pre, dcur, db, dzc);
+        wave_sync();
+        // dW += dPre X^T, both operands read transposed
+#pragma unroll
+        for (int i = 0; i < 2 * NL; ++i) {
+            bf16x4 xt[T];
+#pragma unroll
+            for (int k = 0; k < T; ++k) xt[k] = tile_get_t(L.act[i] + kTile * k);
+#pragma unroll
+            for (int o = 0; o < T; ++o) {
+                const bf16x4 dt = tile_get_t(L.dpre[i] + kTile * o);
+#pragma unroll
+                for (int k = 0; k < T; ++k) dw[i][o][k] = mfma_bf16(dt, xt[k], dw[i][o][k]);
+            }
+        }
+        if (lane < 16) {
+            float kl = 0.0f, nll = 0.0f;
+            for (int i = 0; i < Lt; ++i) kl = __builtin_fmaf(0.5f, L.kl[i][c], kl);
+            for (int k = 0; k < P; ++k) nll = __builtin_fmaf(0.5f, L.nll[k][c], nll);
+            kl_acc += (double)kl;
+            nll_acc += (double)nll;
+        }
         wave_sync();
     }
 
     // bias gradients: sum over the 16 sample columns of each lane group
 #pragma unroll
-    for (int i = 0; i < 2 * nl; ++i) {
+    for (int i = 0; i < 2 * NL; ++i) {
 #pragma unroll
         for (int o = 0; o < T; ++o) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v = db[i][o][q];
-                v += __shfl_xor(v, 1);
-                v += __shfl_xor(v, 2);
-                v += __shfl_xor(v, 4);
-                v += __shfl_xor(v, 8);
-                db[i][o][q] = v;
-            }
+            for (int q = 0; q < 4; ++q) db[i][o][q] = row_sum(db[i][o][q]);
         }
     }
-    // block reduction through LDS (reusing the tile space): the waves add
-    // their gradients into one buffer one after the other, a fixed order
-    const int n_params = 2 * nl * LF;
-    float* red = reinterpret_cast<float*>(lds_all);  // [n_params]
-    static_assert(sizeof(lds_all) >= sizeof(float) * 2 * kMaxNL * LF, "gradient buffer exceeds the LDS tiles");
-    const int c = frag_row(), k0 = frag_k0();
-    for (int w = 0; w < kTrainWaves; ++w) {
-        __syncthreads();
-        if (wave != w) continue;
+    // Block sum through LDS (reusing the tile space), ((w0 + w1) + w2) + w3 of
+    // the waves' gradients: as many waves at a time as there is room for (four,
+    // or three of the two-tile networks).
+    constexpr int kFit = (int)(sizeof(lds_all) / (sizeof(float) * kParams));
+    constexpr int kRegions = kFit < kTrainWaves ? kFit : kTrainWaves;
+    static_assert(kRegions >= 3, "the block sum takes at most two rounds");
+    float* red = reinterpret_cast<float*>(lds_all);  // [kRegions][kParams]
+    auto put = [&](int region) __attribute__((always_inline)) {
+        float* dst = red + region * kParams;
 #pragma unroll
-        for (int i = 0; i < 2 * nl; ++i) {
+        for (int i = 0; i < 2 * NL; ++i) {
 #pragma unroll
             for (int o = 0; o < T; ++o) {
 #pragma unroll
                 for (int k = 0; k < T; ++k) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float& dst = red[i * LF + (kTile * o + k0 + q) * S + kTile * k + c];
-                        dst = w == 0 ? dw[i][o][k][q] : dst + dw[i][o][k][q];
-                    }
+                    for (int q = 0; q < 4; ++q)
+                        dst[i * LF + (kTile * o + k0 + q) * S + kTile * k + c] = dw[i][o][k][q];
                 }
-                if (c == 0) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float& dst = red[i * LF + S * S + kTile * o + k0 + q];
-                        dst = w == 0 ? db[i][o][q] : dst + db[i][o][q];
-                    }
-                }
+                if (c == 0) *reinterpret_cast<f32x4*>(dst + i * LF + S * S + kTile * o + k0) = db[i][o];
             }
         }
-    }
+    };
+    float* partial = a.partial + (int64_t)blockIdx.x * kParams;
     __syncthreads();
-    for (int p = threadIdx.x; p < n_params; p += blockDim.x) a.partial[(int64_t)blockIdx.x * n_params + p] = red[p];
+    if (wave < kRegions) put(wave);
+    __syncthreads();
+    if (kRegions < kTrainWaves) {
+        for (int p = threadIdx.x; p < kParams; p += 256) red[p] = (red[p] + red[kParams + p]) + red[2 * kParams + p];
+        __syncthreads();
+        if (wave == kTrainWaves - 1) put(1);
+        __syncthreads();
+        for (int p = threadIdx.x; p < kParams; p += 256) partial[p] = red[p] + red[kParams + p];
+    } else {
+        for (int p = threadIdx.x; p < kParams; p += 256)
+            partial[p] = ((red[p] + red[kParams + p]) + red[2 * kParams + p]) + red[3 * kParams + p];
+    }
     // loss partials: lanes 0..15 of each wave hold sums
-    __syncthreads();
-    double* dred = reinterpret_cast<double*>(lds_all);
-    if (lane < 16) {
-        dred[(wave * 16 + lane) * 2 + 0] = kl_acc;
-        dred[(wave * 16 + lane) * 2 + 1] = nll_acc;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+        kl_acc += __shfl_xor(kl_acc, off);
+        nll_acc += __shfl_xor(nll_acc, off);
+    }
+    __shared__ double loss_w[kTrainWaves][2];
+    if (lane == 0) {
+        loss_w[wave][0] = kl_acc;
+        loss_w[wave][1] = nll_acc;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double k = 0.0, n = 0.0;
-        for (int i = 0; i < kTrainWaves * 16; ++i) {
-            k += dred[i * 2 + 0];
-            n += dred[i * 2 + 1];
-        }
-        a.loss_partial[blockIdx.x * 2 + 0] = k;
-        a.loss_partial[blockIdx.x * 2 + 1] = n;
+    if (threadIdx.x < 2) {
+        double v = 0.0;
+        for (int w = 0; w < kTrainWaves; ++w) v += loss_w[w][threadIdx.x];
+        a.loss_partial[blockIdx.x * 2 + threadIdx.x] = v;
     }
 }
 
