@@ -593,17 +593,17 @@ __device__ __forceinline__ float one_minus_exp_neg(float x) {
 
 // Lambda^(N) = Sum_{i<=N} albedo^i = albedo (1 - albedo^N) / (1 - albedo),
 // bounded by albedo / (1 - albedo) for any N.
-__device__ __forceinline__ float lambda_total(const RenderArgs& A, float N) {
-    if (A.albedo >= 1.0f) return N;
-    return fast_div(A.albedo * one_minus_exp_neg(-N * A.ln_albedo), 1.0f - A.albedo);
+__device__ __forceinline__ float lambda_total(float albedo, float ln_albedo, float N) {
+    if (albedo >= 1.0f) return N;
+    return fast_div(albedo * one_minus_exp_neg(-N * ln_albedo), 1.0f - albedo);
 }
 
 // Lambda^(N) / albedo^N = albedo (albedo^-N - 1) / (1 - albedo), the weight
 // of a surviving step; it only matters while albedo^N >= 2^-24 (a survivor),
 // so the exponent is capped where it would overflow.
-__device__ __forceinline__ float lambda_weight(const RenderArgs& A, float N) {
-    if (A.albedo >= 1.0f) return N;
-    return fast_div(A.albedo * exp_minus_one(__builtin_fminf(80.0f, -N * A.ln_albedo)), 1.0f - A.albedo);
+__device__ __forceinline__ float lambda_weight(float albedo, float ln_albedo, float N) {
+    if (albedo >= 1.0f) return N;
+    return fast_div(albedo * exp_minus_one(__builtin_fminf(80.0f, -N * ln_albedo)), 1.0f - albedo);
 }
 
 // Writes this lane's part of its decoder input row -- the standardised
@@ -670,9 +670,12 @@ __device__ __forceinline__ void stage_normals(const RenderArgs& A, const PackedM
 }
 
 // Runs one decoder over the first n compacted rows (16-path MFMA tiles);
-// each row's (mean, log variance) outputs overwrite its inputs.
+// each row's (mean, log variance) outputs overwrite its inputs.  FRESH: the
+// weights' addresses are made here, not held in registers through the flights.
+template <bool FRESH>
 __device__ __forceinline__ void decode_tiles(const PackedModel* pm, RenderLds& L, int n) {
     wave_sync();
+    if (FRESH) asm volatile("" : "+s"(pm));
     const int n_tiles = (n + 15) >> 4;
     if (pm->n_linear == kDecLayers) {
         const DecoderRegs w = load_decoder(pm);
@@ -708,10 +711,10 @@ __device__ __forceinline__ void read_row(const PackedModel* pm, const RenderLds&
 }
 
 // decode_tiles, then the sample of row `slot` for lanes that staged one.
-template <int PO>
+template <bool FRESH, int PO>
 __device__ __forceinline__ void decode_rows(const PackedModel* pm, RenderLds& L, bool mine, int slot, int n,
                                             float* y) {
-    decode_tiles(pm, L, n);
+    decode_tiles<FRESH>(pm, L, n);
     if (mine) read_row<PO>(pm, L, slot, y);
     wave_sync();
 }
@@ -936,7 +939,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                                     if (!(u01(wa.x) <= fast_exp(N * A.ln_albedo))) {
                                         path_end = true;
                                     } else {
-                                        Lp += lambda_weight(A, N) * G.light(A, Xk, Wk);
+                                        Lp += lambda_weight(A.albedo, A.ln_albedo, N) * G.light(A, Xk, Wk);
                                         o = x;
                                         d = dir;
                                         G.set_ray(o, d);
@@ -988,6 +991,15 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     // direction.
     auto learned_core = [&](uint64_t wmask, bool mine, V3& po, V3& pd, float pr, const Rng& prng, uint32_t& pc0,
                             float& pLp, uint32_t& pst) __attribute__((always_inline)) -> bool {
+        // What follows from these alone, and the weights' addresses, is worked
+        // out here: held through the flights it cost the kernels of few
+        // primitives 17 spilled registers (the learned 512^2 x 256 image 15.1
+        // ms, so 14.5).  The many-sphere kernels, whose state is in LDS, are
+        // the faster for holding it (53.4 ms, so 55.0).
+        constexpr bool kFresh = !kWaveLight;
+        float albedo = A.albedo;
+        int nee_chain = A.nee_chain;
+        if (kFresh) asm volatile("" : "+s"(albedo), "+s"(nee_chain));
         const int n_wait = __popcll(wmask);
         float y[6];
         float N = 1.0f, psi = 0.0f;
@@ -999,7 +1011,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             stage_row<1, 2>(A.pm[0], L, slot0, prng, pc0, c2);
         }
         stage_normals<1>(A, A.pm[0], L, n_wait);
-        decode_rows<1>(A.pm[0], L, mine, slot0, n_wait, y);
+        decode_rows<kFresh, 1>(A.pm[0], L, mine, slot0, n_wait, y);
         bool alive = false;
         float u_hg = 0.5f, u_first = 1.0f, phiN = 1.0f;
         if (mine) {
@@ -1029,20 +1041,20 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         const bool use_path = lit && (N >= 2.0f || paper);
         // Lambda and Lambda / albedo^N each in a form that stays finite
         // for any N (their product form overflows once albedo^-N does)
-        const float lam = lambda_total(A, N);
+        const float lam = lambda_total(albedo, A.ln_albedo, N);
         // this step's representative events: nee_samples, or with nee_chain
         // one more per nee_chain events of the chain, up to nee_samples (an
         // integer rule on N, so that the draws follow N alone): event k > 0
         // exists iff N - 1 >= k nee_chain
         auto events_of = [&](float n) __attribute__((always_inline)) -> int {
-            if (A.nee_chain <= 0) return A.nee_samples;
-            const uint32_t more = ((uint32_t)n - 1u) / (uint32_t)A.nee_chain;
+            if (nee_chain <= 0) return A.nee_samples;
+            const uint32_t more = ((uint32_t)n - 1u) / (uint32_t)nee_chain;
             return more + 1u < (uint32_t)A.nee_samples ? (int)more + 1 : A.nee_samples;
         };
         auto has_event = [&](int k) __attribute__((always_inline)) -> bool {
-            return A.nee_chain <= 0 || k == 0 || (uint32_t)N - 1u >= (uint32_t)k * (uint32_t)A.nee_chain;
+            return nee_chain <= 0 || k == 0 || (uint32_t)N - 1u >= (uint32_t)k * (uint32_t)nee_chain;
         };
-        const float w_nee = (before ? lam : lambda_weight(A, N)) / (float)events_of(N);
+        const float w_nee = (before ? lam : lambda_weight(albedo, A.ln_albedo, N)) / (float)events_of(N);
         float ct = 0.0f, al = 0.0f, be = 0.0f, ga = 1.0f;
         if (lit && !use_path) ct = hg_sample(cold_hg(), u_hg).mu;
         const uint64_t pmask = ballot(use_path);
@@ -1055,7 +1067,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 stage_row<3, 3>(A.pm[1], L, row, prng, pc0, c3);
             }
             stage_normals<3>(A, A.pm[1], L, __popcll(pmask));
-            decode_rows<3>(A.pm[1], L, use_path, row, __popcll(pmask), y);
+            decode_rows<kFresh, 3>(A.pm[1], L, use_path, row, __popcll(pmask), y);
             if (use_path) {
                 ct = __builtin_fminf(1.0f, __builtin_fmaxf(-1.0f, y[0]));
                 al = y[1];
@@ -1080,7 +1092,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         // (a lane's rows consecutive), as many events per group as 64 rows
         // hold.  The groups run to the wave's largest event count.
         int k_all = A.nee_samples;
-        if (A.nee_chain > 0) {
+        if (nee_chain > 0) {
             float n_max = lit ? N : 1.0f;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) n_max = __builtin_fmaxf(n_max, __shfl_xor(n_max, off));
@@ -1090,7 +1102,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         const int n_cand = __popcll(ballot(use_path));
         const int group = n_cand > 0 ? (64 / n_cand < 1 ? 1 : 64 / n_cand) : k_all;
         const int nb_ev = (A.pm[2]->latent + 6 + 3) >> 2;
-        const float c7[7] = {lst, A.g, A.albedo, ct, al, be, lnN};
+        const float c7[7] = {lst, A.g, albedo, ct, al, be, lnN};
         for (int ka = 0; ka < k_all; ka += group) {
             const int kb = ka + group < k_all ? ka + group : k_all;
             // decisions and draw positions of the group's events
@@ -1103,7 +1115,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 float uf = u_first;
                 if (k > 0 && has) uf = u01(prng.block(pc0++).x);
                 if (has) evbits |= 1u << (16 + k - ka);
-                if (use_path && has && (paper || !(uf * lam <= A.albedo))) {
+                if (use_path && has && (paper || !(uf * lam <= albedo))) {
                     evbits |= 1u << (k - ka);
                     pc0 += (uint32_t)nb_ev;
                 }
@@ -1119,7 +1131,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     if ((evbits >> (k - ka)) & 1u) stage_row<6, 7>(A.pm[2], L, base + j++, prng, c, c7);
                 }
                 stage_normals<6>(A, A.pm[2], L, n_rows);
-                decode_tiles(A.pm[2], L, n_rows);
+                decode_tiles<kFresh>(A.pm[2], L, n_rows);
             }
             int j = 0;
             for (int k = ka; k < kb; ++k) {
@@ -1187,15 +1199,20 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     // about 40 instructions a collision), and then each check one of them
     // against the boundary and trace its shadow ray.  The path goes on from the
     // first flight that did leave, or ends where it was absorbed; the light
-    // is added up in the order of the collisions, as one lane does.  (Bound by
+    // is added up in the order of the collisions, as one lane does.  Where a
+    // learned step is due, at the first collision deep enough for one, the
+    // path waits for the next learned pass of the wave.  (Bound by
     // the issue of one wave, an instruction every 6 cycles; meshes by the
     // latency of the traversals, now G at a time.)  A 99 x 75 x 4 preview of
     // the sphere and box 650 -> 157 us, of a mesh 8.4 -> 1.6 ms; the 512^2 x 256
-    // image's last paths 15.5 -> 13.8 ms.
+    // image's last paths 15.5 -> 13.8 ms; with learned steps 48 x 48 x 4 of it
+    // 0.71 -> 0.15 ms and of 64 spheres 4.9 -> 1.0 ms.
+    constexpr bool kSteps = MODE == kModeStCvae;
     auto trace_together = [&]() __attribute__((always_inline)) {
         const int lane = lane_id();
         int home = tid;
-        bool live = state == S_FLY, leader = true;
+        bool live = state == S_FLY || state == S_WAIT, leader = true;
+        bool wait = state == S_WAIT;  // for a learned step about o
         for (uint64_t left = ballot(live); left != 0; left = ballot(live && leader)) {
             const int n_live = __popcll(left);
             const int lg = n_live > 1 ? 6 - (32 - __builtin_clz((uint32_t)(n_live - 1))) : 6;
@@ -1216,12 +1233,38 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             d = v3(fromf(d.x), fromf(d.y), fromf(d.z));
             t = fromf(t);
             Lp = fromf(Lp);
+            if constexpr (kSteps) {
+                p_st = from(p_st);
+                r_step = fromf(r_step);
+                wait = from(wait ? 1u : 0u) != 0u;
+            }
             live = chain < n_live;
             leader = mine == 0;
             const uint64_t my_bits = (lg == 6 ? ~0ull : (1ull << GL) - 1) << (chain << lg & 63);
             int n_now = n_live;
             bool redo = false;  // the next flight does not end where following it would
             do {
+                bool ended = false, truncated = false;
+                if constexpr (kSteps) {
+                    // learned steps of the paths waiting for one, on one lane
+                    // of each
+                    const bool stepping = live && wait && leader;
+                    const uint64_t smask = ballot(stepping);
+                    if (smask != 0) {
+                        const bool alive = learned_core(smask, stepping, o, d, r_step, rng, c0, Lp, p_st);
+                        const int first = lane - mine;
+                        c0 = (uint32_t)__shfl((int)c0, first);
+                        p_st = (uint32_t)__shfl((int)p_st, first);
+                        o = v3(__shfl(o.x, first), __shfl(o.y, first), __shfl(o.z, first));
+                        d = v3(__shfl(d.x, first), __shfl(d.y, first), __shfl(d.z, first));
+                        Lp = __shfl(Lp, first);
+                        if (live && wait) {
+                            ended = __shfl(alive ? 1 : 0, first) == 0;
+                            t = 0.0f;
+                        }
+                        wait = false;
+                    }
+                }
                 const uint4 w = rng.block(c0 + (uint32_t)mine);
                 const HgSample h = hg_sample(cold_hg(), u01(w.y));
                 const float az = u01(w.z), l_mine = -flight_ln(u01(w.x)) * A.inv_sigma_t;
@@ -1246,24 +1289,30 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     ft += l;
                     return 0;
                 };
-                bool ended = false, truncated = false;
                 uint32_t e0 = 0;
                 // Flights that do not start at a collision (camera rays, rays
                 // going on from the boundary), and at the event limit.
                 for (;;) {
-                    const bool exact = live && !ended && e0 < (uint32_t)GL && (redo || t != 0.0f || p_ev == 0u || p_ev >= A.max_events);
+                    const bool exact = live && !ended && !wait && e0 < (uint32_t)GL &&
+                                       (redo || t != 0.0f || p_ev + p_st == 0u || p_ev + p_st >= A.max_events);
                     if (ballot(exact) == 0) break;
                     if (exact) {
                         redo = false;
                         const int at = slot0 + (int)e0;
-                        const int out = fly(o, d, t, T.flight[at], p_ev == 0u);
+                        const int out = fly(o, d, t, T.flight[at], p_ev + p_st == 0u);
                         if (out == 2) {
                             ended = true;
                         } else if (out == 0) {
-                            if (p_ev >= A.max_events) {
+                            const V3 p = fma3(t, d, o);
+                            float r = 0.0f;
+                            if constexpr (kSteps) r = __builtin_fminf(G.radius(A, p), A.r_cap);
+                            if (p_ev + p_st >= A.max_events) {
                                 ended = truncated = true;
+                            } else if (kSteps && A.sigma_t * r >= A.tau_min) {
+                                wait = true;
+                                r_step = r;
+                                o = p;
                             } else {
-                                const V3 p = fma3(t, d, o);
                                 ++p_ev;
                                 T.pos[at] = make_float4(p.x, p.y, p.z, 0.0f);
                                 T.dir[at] = make_float4(d.x, d.y, d.z, 0.0f);
@@ -1283,18 +1332,18 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 }
                 // as many flights for every path, none past the event limit
                 uint32_t room = (uint32_t)GL;
-                if (live && !ended) {
+                const bool run = live && !ended && !wait;
+                if (run) {
                     room = (uint32_t)GL - e0;
-                    if (A.max_events - p_ev < room) room = A.max_events - p_ev;
+                    if (A.max_events - p_ev - p_st < room) room = A.max_events - p_ev - p_st;
                 }
 #pragma unroll
                 for (int off = 32; off > 0; off >>= 1) {
                     const uint32_t v = (uint32_t)__shfl_xor((int)room, off);
                     room = v < room ? v : room;
                 }
-                const bool run = live && !ended;
                 const uint32_t steps = ballot(run) != 0 ? uniform_u32(room) : 0u;
-                const V3 o_first = o;
+                const V3 o_first = o, d_first = d;
                 {
                     // a path that ended has its last collisions in the slots:
                     // it follows along without writing
@@ -1310,6 +1359,11 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                         d = turn(d, r.x, r.y, r.z, r.w);
                         o = p;
                     }
+                    // a path waiting for a learned step stays where it is
+                    if (kSteps && !run) {
+                        o = o_first;
+                        d = d_first;
+                    }
                 }
                 wave_sync();
                 // each lane checks its flight
@@ -1317,7 +1371,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 const float4 dm = T.dir[slot0 + mine], pm = T.pos[slot0 + mine];
                 const V3 d_mine = v3(dm.x, dm.y, dm.z), p_mine = v3(pm.x, pm.y, pm.z);
                 int out = 0;
-                float t_mine = 0.0f;
+                float t_mine = 0.0f, r_mine = 0.0f;
                 V3 o_mine = o_first;
                 if (followed) {
                     if ((uint32_t)mine > e0) {
@@ -1327,12 +1381,19 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     out = fly(o_mine, d_mine, t_mine, l_mine, false);
                     // it began outside the body by a rounding
                     if (out == 0 && t_mine != l_mine) out = 3;
+                    if (kSteps && out == 0) r_mine = __builtin_fminf(G.radius(A, p_mine), A.r_cap);
                 }
                 const uint64_t followed_m = ballot(followed) & my_bits;
                 const uint64_t left_m = ballot(followed && out != 0) & my_bits, abs_m = absorbed & followed_m;
-                // the first flight that left, the first collision that absorbed
+                // the first flight that left, the first collision that absorbed,
+                // the first one deep enough for a learned step
                 const int f_left = left_m ? __builtin_ctzll(left_m) : 64, f_abs = abs_m ? __builtin_ctzll(abs_m) : 64;
-                const bool valid = followed && lane < f_left && lane <= f_abs;
+                int f_step = 64;
+                if constexpr (kSteps) {
+                    const uint64_t step_m = ballot(followed && out == 0 && A.sigma_t * r_mine >= A.tau_min) & my_bits;
+                    f_step = step_m ? __builtin_ctzll(step_m) : 64;
+                }
+                const bool valid = followed && lane < f_left && lane <= f_abs && lane < f_step;
                 const bool lit = valid || T.light[slot0 + mine] != 0.0f;
                 float light = 0.0f;
                 if constexpr (kWaveLight) {
@@ -1349,7 +1410,15 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 c0 += e0 + (run ? steps : 0u);
                 if (run) {
                     p_ev += (uint32_t)__popcll(valid_m);
-                    if (f_abs < f_left) {
+                    if (kSteps && f_step < f_left && f_step <= f_abs) {
+                        // on to the learned step
+                        const int at = slot0 + f_step - (chain << lg);
+                        c0 -= e0 + steps - (uint32_t)(f_step - (chain << lg)) - 1u;
+                        const float4 df = T.dir[at], pf = T.pos[at];
+                        d = v3(df.x, df.y, df.z);
+                        o = v3(pf.x, pf.y, pf.z);
+                        wait = true;
+                    } else if (f_abs < f_left) {
                         ended = true;
                     } else if (f_left < 64) {
                         // back to the flight that left
@@ -1367,7 +1436,11 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 }
                 const int out_f = __shfl(out, f_left & 63);
                 const float t_f = __shfl(t_mine, f_left & 63);
-                if (run && !ended && f_left < 64) {
+                if constexpr (kSteps) {
+                    const float r_f = __shfl(r_mine, f_step & 63);
+                    if (run && wait) r_step = r_f;
+                }
+                if (run && !ended && !wait && f_left < 64) {
                     if (out_f == 2) ended = true;
                     redo = out_f == 3;
                     c0 -= redo ? 1u : 0u;
@@ -1400,7 +1473,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     for (;;) {
         if (restart_due) restart();
         if (ballot(state != S_DONE) == 0) break;
-        if constexpr (MODE == kModePlain) {
+        if constexpr (MODE != kModeStExact) {
             if (pool.dry && __popcll(ballot(state != S_DONE)) <= kTraceTogether) {
                 trace_together();
                 break;
@@ -1435,10 +1508,11 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
 // (three waves) despite a few spilled registers.
 template <int MODE, int NP, bool GRID>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(const RenderArgs A) {
-    // decoder rows (learned steps) and paths traced together (plain tracing):
-    // an instance only allocates what it uses
-    __shared__ RenderLds lds_rows[kRenderWaves];
-    __shared__ TogetherLds lds_paths[kRenderWaves];
+    // a wave's decoder rows (learned steps) or, between them, the paths that it
+    // traces together
+    constexpr size_t kWaveBytes = MODE == kModeStCvae && sizeof(RenderLds) > sizeof(TogetherLds) ? sizeof(RenderLds)
+                                                                                                  : sizeof(TogetherLds);
+    __shared__ __align__(16) unsigned char lds_wave[kRenderWaves][kWaveBytes];
     __shared__ uint32_t lds_tot[kLaneWords][64 * kRenderWaves];
     // many primitives: the scene's n_prims x 8 floats in dynamic LDS, sized
     // at launch, so that the usual scenes (64 spheres: 2 KB) leave room for
@@ -1446,8 +1520,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     extern __shared__ float lds_dyn[];
     __shared__ float lds_none[8];
     float* lds_prims = NP == 0 ? lds_dyn : lds_none;
-    RenderLds& L = lds_rows[threadIdx.x >> 6];
-    TogetherLds& T = lds_paths[threadIdx.x >> 6];
+    RenderLds& L = *reinterpret_cast<RenderLds*>(lds_wave[threadIdx.x >> 6]);
+    TogetherLds& T = *reinterpret_cast<TogetherLds*>(lds_wave[threadIdx.x >> 6]);
     __shared__ BlockTotals totals;
     // refused models: nothing is traced; a launch that traces plainly queues
     // the plain kernel beside the sphere tracer's, and the other one returns
@@ -1772,7 +1846,6 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
         if (h.blocks > most) h.blocks = most;
         return h;
     };
-    const Shape plain = shape(true), st_shape = shape(false);
     int mode = desc->method == MS_METHOD_PLAIN_NEE ? kModePlain
                : (desc->sampler == MS_SAMPLER_EXACT_WALK ? kModeStExact : kModeStCvae);
     const bool grid_r = A.grid != nullptr;
@@ -1780,7 +1853,7 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     // choice, between two queued kernels
     A.gated = mode != kModePlain && !mesh && !grid_r && A.n_prims <= 4;
     if (mode != kModePlain && !A.gated && traces_plainly(A, INFINITY)) mode = kModePlain;
-    const Shape own = mode == kModePlain ? plain : st_shape;
+    const Shape plain = shape(true), own = mode == kModeStExact ? shape(false) : plain;
     hipLaunchKernelGGL(render_start_kernel, dim3(1), dim3(64), 0, hs, A, learned ? 1 : 0, own.first(), plain.first());
     MS_LAUNCHED();
     auto launch = [&](int m, const Shape& h) {

@@ -612,3 +612,23 @@ def test_paths_traced_together_are_the_same(msst, name, sigma_t, albedo, kw):
     for k in wide:
         assert torch.equal(wide[k], spread[k]), (k, int((wide[k] != spread[k]).sum()))
     assert int(wide["counters"][1]) > 1000
+
+
+@pytest.mark.parametrize("name", ["sphere", "two", "four", "many", "many_grid", "mesh"])
+@pytest.mark.parametrize("sigma_t,albedo,kw", [(20.0, 0.995, dict(spp=2, tau_min=3.0)),
+                                               (80.0, 0.9999, dict(spp=1, tau_min=10.0, flags=3, nee_samples=2)),
+                                               (30.0, 1.0, dict(spp=2, tau_min=3.0, max_events=5))])
+def test_learned_paths_traced_together_are_the_same(msst, oracle, name, sigma_t, albedo, kw):
+    """As above with learned steps: a path waits for one at its first
+    collision, at a later one of the flights followed at once, and again after
+    the step, which counts towards the event limit."""
+    announce(f"render learned together {name} sigma_t={sigma_t} {kw}")
+    packed = pack_all(msst, models_for_test(oracle)[1])
+    r = together_scene(msst, name, 300, 240)
+    med = dict(sigma_t=sigma_t, g=0.8, albedo=albedo)
+    opts = dict(method=ST, sampler=CVAE, packed=packed, min_chain=0.0, seed=6, chunk=1, **kw)
+    wide = r.render(med, blocks_per_cu=1, **opts)
+    spread = r.render(med, blocks_per_cu=64, **opts)
+    for k in wide:
+        assert torch.equal(wide[k], spread[k]), (k, int((wide[k] != spread[k]).sum()))
+    assert int(wide["counters"][2]) > 100
