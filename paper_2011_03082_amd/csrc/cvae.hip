@@ -995,72 +995,129 @@ __global__ void cvae_pack_kernel(Shape s, const float* master, const double* sta
 }
 
 // ---------------------------------------------------------------------------
-// decoder-only sampling: 64 paths per wave = four 16-path MFMA tiles
+// decoder-only sampling: a wave takes 64 / T rows at a time, T lanes each to
+// draw and standardise, then 16-row MFMA tiles
 
 constexpr int kSampleWaves = 4;
 
+// A wave's rows in LDS, feature-major: 16 T decoder inputs, which the outputs
+// overwrite, then 8 T normals of the posterior noise.  Four more columns than
+// rows put a tile's four feature groups on banks of their own, and a lane's
+// own row is without conflicts (row-major, 64 lanes' rows lay on four banks).
 template <int T>
 struct SampleLds {
-    float x[64][kTile * T];
-    float o[64][kTile * T];
+    static constexpr int kRows = 64 / T;
+    float x[kTile * T][kRows + 4];
+    float eps[kTile / 2 * T][kRows + 4];
 };
 
-// T: tiles per layer dimension of the packed model (pm->blocks).
+// T: tiles per layer dimension of the packed model (pm->blocks).  Bound by
+// instruction issue: of about 600 a row set the softplus is half, the normals a
+// third.  Hence no constants of the model held across rows (scalar loads where
+// they are used leave registers for a fifth wave), matrix instructions on
+// vector registers (the attribute of the kernel: without it every tile moves
+// 24 values to and from accumulators), and values converted in pairs.  2^24
+// EventGen samples 557 -> 361 us in BF16, 578 -> 414 in FP8 (moving their 52
+// bytes a row takes 173), of Table 1's widest 1764 -> 870; 1000 samples 9.2 ->
+// 6.8 us.
 template <int T>
-__global__ __launch_bounds__(256) void cvae_sample_kernel(const PackedModel* pm, const float* cond, int64_t n,
-                                                          uint64_t seed, uint64_t id_offset, float* out) {
-    if ((pm->blocks == 2) != (T == 2)) return;
-    __shared__ SampleLds<T> lds_all[kSampleWaves];
-    SampleLds<T>& L = lds_all[threadIdx.x >> 6];
-    const int lane = lane_id();
-    const int P = pm->p_out, Lt = pm->latent, C = pm->p_in;
-    const int64_t n_chunks = (n + 63) / 64;
-    const int64_t wave_global = blockIdx.x * (int64_t)kSampleWaves + (threadIdx.x >> 6);
-    const int64_t n_waves = (int64_t)gridDim.x * kSampleWaves;
-    const bool three = pm->n_linear == kDecLayers;
+__device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* cond, int64_t n, uint64_t seed,
+                                            uint64_t id_offset, float* out, SampleLds<T>& L) {
+    constexpr int R = SampleLds<T>::kRows, kCond = kTile / T, kOut = kTile / 2;
+    const ConstModel c = (ConstModel)pm;
+    const int P = c->p_out, Lt = c->latent, C = c->p_in;
+    // this lane's row of a chunk; of a row's T lanes it takes every T-th
+    // condition, block of normals and output from `part` on
+    const int row = T == 1 ? lane_id() : lane_id() % R, part = T == 1 ? 0 : lane_id() / R;
+    const int col = frag_row(), k0 = frag_k0();
+    const bool three = c->n_linear == kDecLayers, fp8 = c->precision == MS_PREC_FP8;
     const DecoderRegs w = load_decoder(pm);
-    const bool fp8 = pm->precision == MS_PREC_FP8;
+    const int64_t n_chunks = (n + R - 1) / R;
+    const int64_t wave_global = blockIdx.x * (int64_t)kSampleWaves + uniform_u32(threadIdx.x >> 6);
+    const int64_t n_waves = (int64_t)gridDim.x * kSampleWaves;
     for (int64_t chunk = wave_global; chunk < n_chunks; chunk += n_waves) {
-        const int64_t i = chunk * 64 + lane;
+        const int64_t i = chunk * R + row;
         const bool valid = i < n;
-        float nrm[kTile * T];  // latent + p_out <= 16 T normals
-        for (int q = 0; q < kTile * T; ++q) L.x[lane][q] = 0.0f;
+        float cv[kCond] = {};
         if (valid) {
-            const Rng r = make_rng(seed, MS_TAG_CVAE_SAMPLE, id_offset + (uint64_t)i);
-            for (int j = 0; 4 * j < Lt + P; ++j) normals4(r, (uint32_t)j, nrm + 4 * j);
-            for (int q = 0; q < Lt; ++q) L.x[lane][q] = nrm[q];
-            for (int k = 0; k < C; ++k) L.x[lane][Lt + k] = (cond[i * C + k] - pm->mean_c[k]) * pm->inv_std_c[k];
-        }
-        wave_sync();
-        const int64_t remaining = n - chunk * 64;
-        const int n_tiles = remaining >= 64 ? 4 : (int)((remaining + 15) / 16);
-        for (int t = 0; t < n_tiles; ++t) {
-            const int path = 16 * t + frag_row();
-            if constexpr (T == 1) {
-                const f32x4 xin = *reinterpret_cast<const f32x4*>(&L.x[path][frag_k0()]);
-                const f32x4 o = !three ? decoder_tile_layers(pm, xin) : fp8 ? decoder_tile_fp8(w, xin)
-                                                                            : decoder_tile(w, xin);
-                *reinterpret_cast<f32x4*>(&L.o[path][frag_k0()]) = o;
-            } else {
-                const f32x4 xin[2] = {*reinterpret_cast<const f32x4*>(&L.x[path][frag_k0()]),
-                                      *reinterpret_cast<const f32x4*>(&L.x[path][kTile + frag_k0()])};
-                f32x4 o[2];
-                decoder_tile_wide(pm, xin, o);
-                *reinterpret_cast<f32x4*>(&L.o[path][frag_k0()]) = o[0];
-                *reinterpret_cast<f32x4*>(&L.o[path][kTile + frag_k0()]) = o[1];
+#pragma unroll
+            for (int q = 0; q < kCond; ++q) {
+                const int k = q * T + part;
+                if (k < C) cv[q] = cond[i * C + k];
             }
         }
+        const Rng r = make_rng(seed, MS_TAG_CVAE_SAMPLE, id_offset + (uint64_t)i);
+        for (int j = part; 4 * j < Lt + P; j += T) {
+            float nv[4];
+            const uint4 u = r.block((uint32_t)j);
+            box_muller(u01(u.x), u01(u.y), nv[0], nv[1]);
+            if (4 * j + 2 < Lt + P) box_muller(u01(u.z), u01(u.w), nv[2], nv[3]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = 4 * j + q;
+                if (e < Lt + P) L.x[e < Lt ? e : e + (kTile * T - Lt)][row] = nv[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kCond; ++q) {
+            const int k = q * T + part;
+            if (k < C) L.x[Lt + k][row] = (cv[q] - c->mean_c[k]) * c->inv_std_c[k];
+        }
+        for (int q = Lt + C + part; q < kTile * T; q += T) L.x[q][row] = 0.0f;
+        wave_sync();
+        // each lane overwrites exactly the values that it read
+        auto load = [&](int path, int f0) {
+            return f32x4{L.x[f0 + k0][path], L.x[f0 + k0 + 1][path], L.x[f0 + k0 + 2][path], L.x[f0 + k0 + 3][path]};
+        };
+        auto store = [&](int path, int f0, f32x4 v) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) L.x[f0 + k0 + q][path] = v[q];
+        };
+        if constexpr (T == 1) {
+            if (!three) {
+                for (int t = 0; t < R; t += kTile) store(t + col, 0, decoder_tile_layers(pm, load(t + col, 0)));
+            } else if (fp8) {
+#pragma unroll
+                for (int t = 0; t < R; t += kTile) store(t + col, 0, decoder_tile_fp8(w, load(t + col, 0)));
+            } else {
+#pragma unroll
+                for (int t = 0; t < R; t += kTile) store(t + col, 0, decoder_tile(w, load(t + col, 0)));
+            }
+        } else {
+            f32x4 v[R / kTile][2];
+#pragma unroll
+            for (int t = 0; t < R / kTile; ++t)
+                v[t][0] = load(kTile * t + col, 0), v[t][1] = load(kTile * t + col, kTile);
+            decoder_tiles_wide<R / kTile>(pm, v);
+#pragma unroll
+            for (int t = 0; t < R / kTile; ++t)
+                store(kTile * t + col, 0, v[t][0]), store(kTile * t + col, kTile, v[t][1]);
+        }
         wave_sync();
         if (valid) {
-            for (int k = 0; k < P; ++k) {
-                const float mu = L.o[lane][k];
-                const float lv = clamp_lv(L.o[lane][P + k]);
-                const float y = __builtin_fmaf(fast_exp(0.5f * lv), nrm[Lt + k], mu);
-                out[i * P + k] = __builtin_fmaf(y, pm->std_y[k], pm->mean_y[k]);
+#pragma unroll
+            for (int q = 0; q < kOut; ++q) {
+                const int k = q * T + part;
+                if (k >= P) break;
+                const float y = __builtin_fmaf(fast_exp(0.5f * clamp_lv(L.x[P + k][row])), L.eps[k][row], L.x[k][row]);
+                out[i * P + k] = __builtin_fmaf(y, c->std_y[k], c->mean_y[k]);
             }
         }
         wave_sync();
     }
+}
+
+// One kernel for both widths: the packed model's block count is on the device.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void cvae_sample_kernel(
+    const PackedModel* pm, const float* cond, int64_t n, uint64_t seed, uint64_t id_offset, float* out) {
+    union Lds {
+        SampleLds<1> one;
+        SampleLds<2> two;
+    };
+    __shared__ Lds lds_all[kSampleWaves];
+    Lds& L = lds_all[threadIdx.x >> 6];
+    if (pm->blocks == 2) sample_rows<2>(pm, cond, n, seed, id_offset, out, L.two);
+    else sample_rows<1>(pm, cond, n, seed, id_offset, out, L.one);
 }
 
 // ---------------------------------------------------------------------------
@@ -1427,14 +1484,12 @@ ms_status cvae_sample(const void* packed_dev, const float* cond_dev, int64_t n, 
     ms_status st = device_cu_count(&cus);
     if (st != MS_OK) return st;
     int64_t blocks = (n + 64 * kSampleWaves - 1) / (64 * kSampleWaves);
-    if (blocks > cus * 8) blocks = cus * 8;
-    // the packed model's block count is on the device: each instance returns
-    // at once unless it matches
+    // five blocks fit a CU; shares of a sixth of that even out the end (2^24
+    // samples 380 us with 8 blocks per CU, 367 with 20, 361 with 32 and with 64)
+    if (blocks > cus * 32) blocks = cus * 32;
     const PackedModel* pm = reinterpret_cast<const PackedModel*>(packed_dev);
-    hipLaunchKernelGGL(cvae_sample_kernel<1>, dim3((unsigned)blocks), dim3(64 * kSampleWaves), 0, (hipStream_t)stream,
-                       pm, cond_dev, n, seed, id_offset, out_dev);
-    hipLaunchKernelGGL(cvae_sample_kernel<2>, dim3((unsigned)blocks), dim3(64 * kSampleWaves), 0, (hipStream_t)stream,
-                       pm, cond_dev, n, seed, id_offset, out_dev);
+    hipLaunchKernelGGL(cvae_sample_kernel, dim3((unsigned)blocks), dim3(64 * kSampleWaves), 0, (hipStream_t)stream, pm,
+                       cond_dev, n, seed, id_offset, out_dev);
     MS_LAUNCHED();
     clear_error();
     return MS_OK;

@@ -212,8 +212,13 @@ __device__ __forceinline__ float sphere_exit(V3 x, V3 d, float r2) {
 }
 
 // Softplus log(1 + e^x) = max(x, 0) + log(1 + e^-|x|) and its derivative.
+// The larger of x and 0 is a median with infinity, one instruction; a maximum
+// first quiets x, and the compiler turns a median back into one unless it does
+// not see the infinity.
 __device__ __forceinline__ float softplus(float x) {
-    return __builtin_fmaxf(x, 0.0f) + fast_ln(1.0f + fast_exp(-__builtin_fabsf(x)));
+    float inf = __builtin_inff();
+    asm("" : "+s"(inf));
+    return __builtin_amdgcn_fmed3f(x, 0.0f, inf) + fast_ln(1.0f + fast_exp(-__builtin_fabsf(x)));
 }
 __device__ __forceinline__ float sigmoid(float x) { return fast_rcp(1.0f + fast_exp(-x)); }
 

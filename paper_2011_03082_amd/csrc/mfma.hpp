@@ -26,13 +26,14 @@ __device__ __forceinline__ f32x4 mfma_bf16(bf16x4 a, bf16x4 b, f32x4 c) {
 __device__ __forceinline__ int frag_row() { return lane_id() & 15; }  // A row / B, D column
 __device__ __forceinline__ int frag_k0() { return (lane_id() >> 4) * 4; } // first of 4 K (or D) rows
 
+// Converted in pairs (four values at once, or one by one, the compiler converts
+// each alone and then packs: six instructions instead of two).
 __device__ __forceinline__ bf16x4 to_bf16x4(float a, float b, float c, float d) {
-    bf16x4 r;
-    r[0] = (__bf16)a;
-    r[1] = (__bf16)b;
-    r[2] = (__bf16)c;
-    r[3] = (__bf16)d;
-    return r;
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 lo = __builtin_convertvector((f32x2){a, b}, bf16x2), hi = __builtin_convertvector((f32x2){c, d}, bf16x2);
+    const uint2 u = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+    return __builtin_bit_cast(bf16x4, u);
 }
 __device__ __forceinline__ bf16x4 to_bf16x4(f32x4 v) { return to_bf16x4(v[0], v[1], v[2], v[3]); }
 __device__ __forceinline__ float bf16_round(float x) { return (float)(__bf16)x; }

@@ -37,6 +37,10 @@ struct PackedModel {
     int32_t pad_[3];
 };
 
+// Read by every lane alike, and written by no kernel that reads it so: scalar
+// loads.
+typedef const __attribute__((address_space(4))) PackedModel* ConstModel;
+
 __device__ __forceinline__ const uint32_t* frag_tile(const PackedModel* pm, int layer, int t) {
     return t == 0 ? pm->frag[layer][lane_id()] : pm->frag_hi[layer][t - 1][lane_id()];
 }
@@ -165,47 +169,56 @@ __device__ __forceinline__ f32x4 decoder_tile_layers(const PackedModel* pm, f32x
 }
 
 // Two-block decoders (Table 1's widest settings), any depth: inputs and
-// outputs are 32 features of one 16-path tile, xin[0] rows 0..15 and
-// xin[1] rows 16..31 in D layout; weights read per layer.
-__device__ __forceinline__ void decoder_tile_wide(const PackedModel* pm, const f32x4* xin, f32x4* out) {
+// outputs are 32 features of NT 16-path tiles, v[t][0] rows 0..15 and v[t][1]
+// rows 16..31 in D layout; weights read once per layer.
+template <int NT>
+__device__ __forceinline__ void decoder_tiles_wide(const PackedModel* pm, f32x4 (&v)[NT][2]) {
     const int nl = pm->n_linear;
     const int k0 = frag_k0();
     const bool fp8 = pm->precision == MS_PREC_FP8;
-    f32x4 x[2] = {xin[0], xin[1]};
     for (int j = 0; j < nl; ++j) {
-        f32x4 acc[2];
+        f32x4 acc[NT][2];
+        const f32x4 b[2] = {*reinterpret_cast<const f32x4*>(&pm->bias[j][k0]),
+                            *reinterpret_cast<const f32x4*>(&pm->bias_hi[j][k0])};
+        if (fp8) {
+            const float isc = pm->in_scale[j], sc = pm->out_scale[j];
+            fp8x8 a[2];
 #pragma unroll
-        for (int o = 0; o < 2; ++o) {
-            const f32x4 b = *reinterpret_cast<const f32x4*>(o == 0 ? &pm->bias[j][k0] : &pm->bias_hi[j][k0]);
-            if (fp8) {
+            for (int o = 0; o < 2; ++o) {
                 const uint2 u = *reinterpret_cast<const uint2*>(frag_tile(pm, j, o));
-                const fp8x8 a = (fp8x8)(((uint64_t)u.y << 32) | u.x);
-                const float isc = pm->in_scale[j], sc = pm->out_scale[j];
-                const uint64_t lo = (uint32_t)to_fp8x4_lo(scaled(x[0], isc));
-                const uint64_t hi = (uint32_t)to_fp8x4_lo(scaled(x[1], isc));
-                f32x4 r = mfma_fp8(a, (fp8x8)(lo | (hi << 32)), f32x4{0, 0, 0, 0});
+                a[o] = (fp8x8)(((uint64_t)u.y << 32) | u.x);
+            }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) r[q] = __builtin_fmaf(r[q], sc, b[q]);
-                acc[o] = r;
-            } else {
-                f32x4 r = b;
+            for (int t = 0; t < NT; ++t) {
+                const uint64_t lo = (uint32_t)to_fp8x4_lo(scaled(v[t][0], isc));
+                const uint64_t hi = (uint32_t)to_fp8x4_lo(scaled(v[t][1], isc));
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const uint2 u = *reinterpret_cast<const uint2*>(frag_tile(pm, j, 2 * o + k));
-                    r = mfma_bf16(__builtin_bit_cast(bf16x4, u), to_bf16x4(x[k]), r);
+                for (int o = 0; o < 2; ++o) {
+                    acc[t][o] = mfma_fp8(a[o], (fp8x8)(lo | (hi << 32)), f32x4{0, 0, 0, 0});
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[t][o][q] = __builtin_fmaf(acc[t][o][q], sc, b[o][q]);
                 }
-                acc[o] = r;
+            }
+        } else {
+            bf16x4 a[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                a[q] = __builtin_bit_cast(bf16x4, *reinterpret_cast<const uint2*>(frag_tile(pm, j, q)));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const bf16x4 x[2] = {to_bf16x4(v[t][0]), to_bf16x4(v[t][1])};
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+                    acc[t][o] = mfma_bf16(a[2 * o + 1], x[1], mfma_bf16(a[2 * o], x[0], b[o]));
             }
         }
-        if (j < nl - 1) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
 #pragma unroll
             for (int o = 0; o < 2; ++o) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) x[o][q] = softplus(acc[o][q]);
+                for (int q = 0; q < 4; ++q) v[t][o][q] = j < nl - 1 ? softplus(acc[t][o][q]) : acc[t][o][q];
             }
-        } else {
-            out[0] = acc[0];
-            out[1] = acc[1];
         }
     }
 }

@@ -413,3 +413,39 @@ def test_non_finite_master_weight_shows_in_loss_and_gradient(msst, bad):
     master[int(real[0])] = bad  # first weight of the encoder's first layer
     msst.cvae_train_step(model, master, None, None, None, cd, td, n_rows, B, 0, 5, 1, 0, ws, loss, grad)
     assert not torch.isfinite(loss[0]) and not torch.isfinite(grad).all()
+
+
+@pytest.mark.parametrize("precision", [1, 2])
+@pytest.mark.parametrize("width,latent,n_linear", [(16, 4, 3), (16, 4, 2), (20, 9, 4), (12, 5, 3)])
+@pytest.mark.parametrize("model", MODELS)
+def test_samples_of_few_rows(msst, oracle, model, width, latent, n_linear, precision):
+    """Rows below, at and past a tile, half a wave and a wave, for one- and
+    two-tile decoders of every depth: a row's samples depend on its index
+    alone, and nothing past the last row is written.  Against the oracle that
+    rounds as the kernel does: the median row within the bounds that hold for
+    99 of 100 of the standard decoder, and rows with a flipped rounding within
+    twice its largest difference (up to twice the units and layers)."""
+    announce(f"cvae sample rows model={model} width={width} latent={latent} precision={precision}")
+    shape = dict(W.SHAPE_LIST[model], width=width, latent=latent, n_linear=n_linear)
+    master64 = oracle.cvae_init(shape, seed=90 + model).astype(np.float32).astype(np.float64)
+    stats = W.random_stats(model, seed=30 + model)
+    packed = torch.empty(msst.cvae_packed_bytes(), dtype=torch.uint8, device="cuda")
+    msst.cvae_pack(shape, dev(master64), dev(stats, torch.float64), precision, packed)
+    most = 300
+    cond = W.random_conditions(model, most, seed=40 + model).astype(np.float32)
+    ref = oracle.cvae_sample(shape, master64, stats, cond.astype(np.float64), 3, 1 << 33,
+                             precision=oracle.PREC_BF16 if precision == 1 else oracle.PREC_FP8)
+    P = shape["p_out"]
+    first = None
+    for n in (most, 1, 15, 17, 31, 33, 63, 64, 65, 257):
+        out = torch.full((n * P + 64,), 7.0, dtype=torch.float32, device="cuda")
+        msst.cvae_sample(packed, dev(cond[:n]), n, 3, 1 << 33, out)
+        got = out.cpu().numpy()
+        assert (got[n * P:] == 7.0).all()
+        rows = got[: n * P].reshape(n, P)
+        if first is None:
+            first = rows
+            err = np.abs(rows - ref).max(axis=1) / stats[48:48 + P].max()
+            assert np.median(err) < (1e-4 if precision == 1 else 1e-3) and err.max() < (0.1 if precision == 1 else 0.4)
+        else:
+            np.testing.assert_array_equal(rows, first[:n])
