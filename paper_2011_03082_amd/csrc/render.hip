@@ -279,6 +279,7 @@ __device__ __forceinline__ float nee(const RenderArgs& A, const Prims<NP>& P, V3
 // are computed once per ray and kept in registers.
 template <int NP, bool GRID>
 struct Geo {
+    static constexpr bool kPairs = false;
     static constexpr bool kWaveLight = false;  // shadow rays tested per lane (few primitives)
     Prims<NP> P;
     RayIv<NP> iv;
@@ -314,6 +315,7 @@ constexpr int kHitSlots = 8;
 template <bool GRID>
 struct GeoMany {
     // shadow rays of a wave share a primitive mask (light_mask below)
+    static constexpr bool kPairs = false;
     static constexpr bool kWaveLight = true;
     const float* prim;  // LDS [n][8]
     int n;
@@ -504,7 +506,14 @@ struct GeoMany {
 // point inside the body and entry / exit from the camera; up to four medium
 // intervals are kept in registers.  Radii come from the distance grid;
 // shadow rays traverse their own segment to the light.
+// A wave's shadow rays and their lengths inside the body (by lane).
+struct PairLds {
+    float4 from[64], to[64];
+    float length[64];
+};
+
 struct GeoMesh {
+    static constexpr bool kPairs = true;
     static constexpr bool kWaveLight = false;  // shadow rays traverse the BVH per lane
     const BvhNode* nodes;
     const float* tris;
@@ -518,8 +527,14 @@ struct GeoMesh {
     __device__ __forceinline__ void set_ray(V3 o, V3 d) { set_ray_from(o, d, true); }
     __device__ __forceinline__ void set_camera_ray(V3 o, V3 d) { set_ray_from(o, d, false); }
     __device__ __forceinline__ void set_ray_from(V3 o, V3 d, bool inside) {
-        float c[kMeshCross];
-        const int m = mesh_crossings(nodes, n_nodes, tris, o, d, 0.0f, INFINITY, c);
+        MeshWalk w;
+        w.start(o, d, INFINITY);
+        mesh_crossings(nodes, n_nodes, tris, w);
+        set_intervals(w, inside);
+    }
+    __device__ __forceinline__ void set_intervals(const MeshWalk& w, bool inside) {
+        const float* c = w.c;
+        const int m = w.crossings();
         // inside: (-inf, c0), (c1, c2), (c3, c4), ...; outside: (c0, c1), (c2, c3), ...
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -533,23 +548,87 @@ struct GeoMesh {
     __device__ __forceinline__ float radius(const RenderArgs& A, V3 p) const { return grid_radius(A, p); }
     __device__ __forceinline__ float flight_bound(const RenderArgs&, V3) const { return 0.0f; }
 
+    // length inside the body of a shadow ray from a point inside: inside until
+    // c[0], outside until c[1], ...
+    static __device__ __forceinline__ float length_inside(const MeshWalk& w, float dist) {
+        const int m = w.crossings();
+        float acc = 0.0f, prev = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kMeshCross; ++k)
+            if (k < m) {
+                if ((k & 1) == 0) acc += w.c[k] - prev;
+                prev = w.c[k];
+            }
+        if ((m & 1) == 0) acc += dist - prev;
+        return acc;
+    }
     __device__ __forceinline__ float light(const RenderArgs& A, V3 x, V3 d) const {
         V3 wl = v3(A.light[0] - x.x, A.light[1] - x.y, A.light[2] - x.z);
         const float dist2 = dot(wl, wl);
         const float inv_dist = fast_rsq(dist2);
         const float dist = dist2 * inv_dist;
         wl = inv_dist * wl;
-        float c[kMeshCross];
-        const int m = mesh_crossings(nodes, n_nodes, tris, x, wl, 0.0f, dist, c);
-        // x is inside: inside until c[0], outside until c[1], ...
-        float acc = 0.0f, prev = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kMeshCross; ++k)
-            if (k < m) {
-                if ((k & 1) == 0) acc += c[k] - prev;
-                prev = c[k];
+        MeshWalk w;
+        w.start(x, wl, dist);
+        mesh_crossings(nodes, n_nodes, tris, w);
+        const float acc = length_inside(w, dist);
+        return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
+    }
+
+    // The shadow rays of the lanes in `lit`, from x with direction of flight d,
+    // and the next rays (o, nd) of those in `go`, which start there, traced by
+    // the whole wave: a lane begins with its own next ray, and lanes without a
+    // segment take the next shadow ray that has none.  Returns the light.  (One
+    // after the other the two traversals each ran as long as their longest ray,
+    // with 18 of 64 lanes at a node: a 256^2 x 128 image 37.0 ms, 29.3 so, 28.2
+    // with lanes that leave the nodes at three of eight busy.)
+    __device__ __forceinline__ float light_and_ray(const RenderArgs& A, PairLds& S, bool lit, V3 x, V3 d, bool go, V3 o,
+                                                   V3 nd) {
+        const int lane = lane_id();
+        const uint32_t n = (uint32_t)n_nodes;
+        V3 wl = v3(A.light[0] - x.x, A.light[1] - x.y, A.light[2] - x.z);
+        const float dist2 = dot(wl, wl);
+        const float inv_dist = fast_rsq(dist2);
+        const float dist = dist2 * inv_dist;
+        wl = inv_dist * wl;
+        const uint64_t lits = ballot(lit);
+        if (lit) {
+            const int r = rank_in(lits);
+            S.from[r] = make_float4(x.x, x.y, x.z, dist);
+            S.to[r] = make_float4(wl.x, wl.y, wl.z, __int_as_float(lane));
+        }
+        wave_sync();
+        const int n_lit = __popcll(lits);
+        int next = 0;  // first shadow ray without a lane
+        int owner = go ? lane : -1;  // of the segment: -1 none, + 64 a shadow ray
+        MeshWalk w;
+        if (go) w.start(o, nd, INFINITY);
+        else w.m = w.leaf = 0, w.i = n;
+        for (;;) {
+            if (owner >= 0 && w.done(n)) {
+                if (owner < 64) set_intervals(w, true);
+                else S.length[owner - 64] = length_inside(w, w.thi);
+                owner = -1;
             }
-        if ((m & 1) == 0) acc += dist - prev;
+            if (next < n_lit) {
+                const uint64_t idle = ballot(owner < 0);
+                const int r = next + rank_in(idle);
+                if (owner < 0 && r < n_lit) {
+                    const float4 f = S.from[r], g = S.to[r];
+                    owner = 64 + __float_as_int(g.w);
+                    w.start(v3(f.x, f.y, f.z), v3(g.x, g.y, g.z), f.w);
+                }
+                next += __popcll(idle);
+            }
+            const uint64_t busy = ballot(owner >= 0);
+            if (busy == 0) break;
+            const int stop = __popcll(busy) * 3 >> 3;
+            if (owner >= 0 && w.walks(n)) w.walk(nodes, n, stop);
+            if (owner >= 0 && w.leaf != 0) w.test(tris);
+        }
+        wave_sync();
+        if (!lit) return 0.0f;
+        const float acc = S.length[lane];
         return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
     }
 };
@@ -741,7 +820,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                                             uint32_t (*tot)[64 * kRenderWaves], BlockTotals& totals,
                                             TogetherLds& T) {
     typename GeoSel<NP, GRID>::type G;
-    constexpr bool kWaveLight = GeoSel<NP, GRID>::type::kWaveLight;
+    PairLds& S = *reinterpret_cast<PairLds*>(&T + 1);  // meshes only
+    constexpr bool kWaveLight = GeoSel<NP, GRID>::type::kWaveLight, kPairs = GeoSel<NP, GRID>::type::kPairs;
     G.init(A, lds_prims);
 
     TicketPool pool;
@@ -873,8 +953,9 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     // start of a learned step, for every lane in flight
     auto collide = [&](bool& path_end, bool& truncated) __attribute__((always_inline)) {
         // many primitives: a plain event's shadow ray is traced after the
-        // branch, where the whole wave builds its primitive mask
-        bool nee_now = false;
+        // branch, where the whole wave builds its primitive mask; a mesh's is
+        // traced there too, with the path's next ray
+        bool nee_now = false, ray_now = false;
         V3 nee_x = v3(0, 0, 0), nee_d = v3(0, 0, 1);
         if (state == S_FLY) {
             // one Philox block per flight; the boundary query (the medium
@@ -954,7 +1035,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                         }
                         if (plain) {
                             ++p_ev;
-                            if constexpr (kWaveLight) {
+                            if constexpr (kWaveLight || kPairs) {
                                 nee_now = true;
                                 nee_x = p;
                                 nee_d = d;
@@ -967,7 +1048,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                                 const HgSample h = hg_sample(cold_hg(), u01(w.y));
                                 d = scatter(d, h.mu, h.sin_t, u01(w.z));
                                 o = p;
-                                G.set_ray(o, d);
+                                if constexpr (kPairs) ray_now = true;
+                                else G.set_ray(o, d);
                                 t = 0.0f;
                             }
                         }
@@ -980,6 +1062,10 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             uint64_t mk[kMaxManyPrims / 64];
             G.light_mask(A, nee_now, nee_x, mk);
             if (nee_now) Lp += A.albedo * G.light_masked(A, nee_x, nee_d, mk);
+        }
+        if constexpr (kPairs) {
+            const float li = G.light_and_ray(A, S, nee_now, nee_x, nee_d, ray_now, o, d);
+            if (nee_now) Lp += A.albedo * li;
         }
     };
 
@@ -1204,7 +1290,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     // path waits for the next learned pass of the wave.  (Bound by
     // the issue of one wave, an instruction every 6 cycles; meshes by the
     // latency of the traversals, now G at a time.)  A 99 x 75 x 4 preview of
-    // the sphere and box 650 -> 157 us, of a mesh 8.4 -> 1.6 ms; the 512^2 x 256
+    // the sphere and box 650 -> 157 us, of a mesh 8.4 -> 1.1 ms; the 512^2 x 256
     // image's last paths 15.5 -> 13.8 ms; with learned steps 48 x 48 x 4 of it
     // 0.71 -> 0.15 ms and of 64 spheres 4.9 -> 1.0 ms.
     constexpr bool kSteps = MODE == kModeStCvae;
@@ -1275,9 +1361,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 wave_sync();
                 // A flight of the ray (o, d) from t: its end in t; 0 in the
                 // medium, 1 at the boundary, 2 if the ray leaves for good.
-                auto fly = [&](V3 fo, V3 fd, float& ft, float l, bool camera) __attribute__((always_inline)) -> int {
-                    if (camera) G.set_camera_ray(fo, fd);
-                    else G.set_ray(fo, fd);
+                auto flight = [&](V3 fo, V3 fd, float& ft, float l) __attribute__((always_inline)) -> int {
                     float ps = ft, pe = INFINITY;
                     const bool inside = l < G.flight_bound(A, fma3(ft, fd, fo));
                     if (!inside && !G.piece(fo, fd, ft, ps, pe)) return 2;
@@ -1299,7 +1383,9 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     if (exact) {
                         redo = false;
                         const int at = slot0 + (int)e0;
-                        const int out = fly(o, d, t, T.flight[at], p_ev + p_st == 0u);
+                        if (p_ev + p_st == 0u) G.set_camera_ray(o, d);
+                        else G.set_ray(o, d);
+                        const int out = flight(o, d, t, T.flight[at]);
                         if (out == 2) {
                             ended = true;
                         } else if (out == 0) {
@@ -1373,12 +1459,19 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 int out = 0;
                 float t_mine = 0.0f, r_mine = 0.0f;
                 V3 o_mine = o_first;
+                if (followed && (uint32_t)mine > e0) {
+                    const float4 pp = T.pos[slot0 + mine - 1];
+                    o_mine = v3(pp.x, pp.y, pp.z);
+                }
+                // a mesh's shadow rays are traced with the flights, also those
+                // that turn out not to be needed
+                float light = 0.0f;
+                if constexpr (kPairs)
+                    light = G.light_and_ray(A, S, followed || T.light[slot0 + mine] != 0.0f, p_mine, d_mine, followed,
+                                            o_mine, d_mine);
+                else if (followed) G.set_ray(o_mine, d_mine);
                 if (followed) {
-                    if ((uint32_t)mine > e0) {
-                        const float4 pp = T.pos[slot0 + mine - 1];
-                        o_mine = v3(pp.x, pp.y, pp.z);
-                    }
-                    out = fly(o_mine, d_mine, t_mine, l_mine, false);
+                    out = flight(o_mine, d_mine, t_mine, l_mine);
                     // it began outside the body by a rounding
                     if (out == 0 && t_mine != l_mine) out = 3;
                     if (kSteps && out == 0) r_mine = __builtin_fminf(G.radius(A, p_mine), A.r_cap);
@@ -1395,11 +1488,12 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 }
                 const bool valid = followed && lane < f_left && lane <= f_abs && lane < f_step;
                 const bool lit = valid || T.light[slot0 + mine] != 0.0f;
-                float light = 0.0f;
                 if constexpr (kWaveLight) {
                     uint64_t mk[kMaxManyPrims / 64];
                     G.light_mask(A, lit, p_mine, mk);
                     if (lit) light = G.light_masked(A, p_mine, d_mine, mk);
+                } else if constexpr (kPairs) {
+                    if (!lit) light = 0.0f;
                 } else {
                     if (lit) light = G.light(A, p_mine, d_mine);
                 }
@@ -1510,8 +1604,8 @@ template <int MODE, int NP, bool GRID>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(const RenderArgs A) {
     // a wave's decoder rows (learned steps) or, between them, the paths that it
     // traces together
-    constexpr size_t kWaveBytes = MODE == kModeStCvae && sizeof(RenderLds) > sizeof(TogetherLds) ? sizeof(RenderLds)
-                                                                                                  : sizeof(TogetherLds);
+    constexpr size_t kPathBytes = sizeof(TogetherLds) + (GeoSel<NP, GRID>::type::kPairs ? sizeof(PairLds) : 0);
+    constexpr size_t kWaveBytes = MODE == kModeStCvae && sizeof(RenderLds) > kPathBytes ? sizeof(RenderLds) : kPathBytes;
     __shared__ __align__(16) unsigned char lds_wave[kRenderWaves][kWaveBytes];
     __shared__ uint32_t lds_tot[kLaneWords][64 * kRenderWaves];
     // many primitives: the scene's n_prims x 8 floats in dynamic LDS, sized
