@@ -312,6 +312,24 @@ struct Geo {
 constexpr int kMaxManyPrims = 256;
 constexpr int kHitSlots = 8;
 
+// The hit intervals of one query, the latest first.  A ninth is lost to the
+// slots but counted: the caller then asks anew.  (Moving the slots up is 16
+// moves; comparing the count with each slot took half as many again.)
+struct Hits {
+    float a[kHitSlots], b[kHitSlots];
+    int m = 0;
+    __device__ __forceinline__ void add(float ta, float tb) {
+#pragma unroll
+        for (int j = kHitSlots - 1; j > 0; --j) {
+            a[j] = a[j - 1];
+            b[j] = b[j - 1];
+        }
+        a[0] = ta;
+        b[0] = tb;
+        ++m;
+    }
+};
+
 template <bool GRID>
 struct GeoMany {
     // shadow rays of a wave share a primitive mask (light_mask below)
@@ -326,46 +344,74 @@ struct GeoMany {
     __device__ __forceinline__ void set_ray(V3, V3) {}
     __device__ __forceinline__ void set_camera_ray(V3, V3) {}
     __device__ __forceinline__ bool piece(V3 o, V3 d, float t, float& s, float& e) const {
-        float ca[kHitSlots], cb[kHitSlots];
-        int m = 0;
-        bool overflow = false;
+        piece_of(o, d, t, 0, 1, s, e);
+        return s != INFINITY;
+    }
+    // The medium piece of the ray containing t or following it, (s, e); s is
+    // infinite if it leaves for good.  The primitives first, first + step, ...
+    // are this lane's; the `step` lanes that share a ray are neighbours.
+    __device__ __forceinline__ void piece_of(V3 o, V3 d, float t, int first, int step, float& s, float& e) const {
+        Hits h;
+#pragma unroll
+        for (int j = 0; j < kHitSlots; ++j) h.a[j] = INFINITY, h.b[j] = -INFINITY;
         s = INFINITY;
-        for (int i = 0; i < n; ++i) {
+        for (int i = first; i < n; i += step) {
             float a, b;
             if (prim_interval(prim + 8 * i, o, d, a, b) && b > t) {
                 s = __builtin_fminf(s, __builtin_fmaxf(a, t));
-#pragma unroll
-                for (int j = 0; j < kHitSlots; ++j)
-                    if (j == m) {
-                        ca[j] = a;
-                        cb[j] = b;
-                    }
-                if (m < kHitSlots) ++m;
-                else overflow = true;
+                h.add(a, b);
             }
         }
-        if (s == INFINITY) return false;
+        for (int off = 1; off < step; off <<= 1) s = __builtin_fminf(s, __shfl_xor(s, off));
         e = s;
-        if (!overflow) {
-#pragma unroll
-            for (int pass = 0; pass < kHitSlots; ++pass)
+        if (s == INFINITY) return;
+        // the piece grows by the intervals that begin in it until none is left
+        for (bool grew = true; grew;) {
+            const float e0 = e;
+            if (h.m <= kHitSlots) {
 #pragma unroll
                 for (int j = 0; j < kHitSlots; ++j)
-                    if (j < m && ca[j] <= e && cb[j] > e) e = cb[j];
-        } else {
-            for (int pass = 0; pass < n; ++pass) {
-                bool grew = false;
-                for (int i = 0; i < n; ++i) {
+                    if (h.a[j] <= e && h.b[j] > e) e = h.b[j];
+            } else {
+                for (int i = first; i < n; i += step) {
                     float a, b;
-                    if (prim_interval(prim + 8 * i, o, d, a, b) && a <= e && b > e) {
-                        e = b;
-                        grew = true;
-                    }
+                    if (prim_interval(prim + 8 * i, o, d, a, b) && a <= e && b > e) e = b;
                 }
-                if (!grew) break;
             }
+            for (int off = 1; off < step; off <<= 1) e = __builtin_fmaxf(e, __shfl_xor(e, off));
+            grew = e > e0;
         }
-        return true;
+    }
+    // The same for the lanes in `need` of a converged wave, with direction
+    // dirs[at]: each ray is given 64 / (rays) lanes, which share the primitives.
+    // (Only flights longer than the radius at their start need it, a fifth to
+    // a third of a wave's; on one lane each they took the wave through all
+    // primitives: 512^2 x 32 of 64 spheres 54.0 ms, 41.4 so and with the slots
+    // above.)
+    __device__ __forceinline__ bool wave_piece(float4* from, float* index, const float4* dirs, bool need, V3 o, int at,
+                                               float t, float& s, float& e) const {
+        const uint64_t needs = ballot(need);
+        if (needs == 0) return true;
+        const int n_need = __popcll(needs), r = rank_in(needs);
+        const int lg = n_need > 1 ? 6 - (32 - __builtin_clz((uint32_t)(n_need - 1))) : 6;
+        if (need) {
+            from[r] = make_float4(o.x, o.y, o.z, t);
+            index[r] = __int_as_float(at);
+        }
+        wave_sync();
+        const int ray = lane_id() >> lg, mine = lane_id() - (ray << lg);
+        if (ray < n_need) {
+            const float4 f = from[ray], g = dirs[__float_as_int(index[ray])];
+            float ps, pe;
+            piece_of(v3(f.x, f.y, f.z), v3(g.x, g.y, g.z), f.w, mine, 1 << lg, ps, pe);
+            if (mine == 0) from[ray] = make_float4(ps, pe, 0.0f, 0.0f);
+        }
+        wave_sync();
+        if (!need) return true;
+        const float4 p = from[r];
+        s = p.x;
+        e = p.y;
+        return s != INFINITY;
     }
     __device__ __forceinline__ float radius(const RenderArgs& A, V3 p) const {
         if (GRID) return grid_radius(A, p);
@@ -432,26 +478,13 @@ struct GeoMany {
         const float inv_dist = fast_rsq(dist2);
         const float dist = dist2 * inv_dist;
         wl = inv_dist * wl;
-        float ca[kHitSlots], cb[kHitSlots];
+        Hits h;
 #pragma unroll
-        for (int j = 0; j < kHitSlots; ++j) {
-            ca[j] = INFINITY;
-            cb[j] = INFINITY;
-        }
-        int m = 0;
+        for (int j = 0; j < kHitSlots; ++j) h.a[j] = h.b[j] = INFINITY;
         auto visit = [&](int i) {
             float a, b;
-            if (prim_interval(prim + 8 * i, x, wl, a, b) && b > 0.0f && a < dist) {
-                a = __builtin_fmaxf(a, 0.0f);
-                b = __builtin_fminf(b, dist);
-#pragma unroll
-                for (int j = 0; j < kHitSlots; ++j)
-                    if (j == m) {
-                        ca[j] = a;
-                        cb[j] = b;
-                    }
-                ++m;
-            }
+            if (prim_interval(prim + 8 * i, x, wl, a, b) && b > 0.0f && a < dist)
+                h.add(__builtin_fmaxf(a, 0.0f), __builtin_fminf(b, dist));
         };
         if (mask == nullptr) {
             for (int i = 0; i < n; ++i) visit(i);
@@ -460,34 +493,40 @@ struct GeoMany {
                 for (uint64_t bits = mask[k]; bits != 0; bits &= bits - 1) visit(64 * k + __builtin_ctzll(bits));
         }
         float acc = 0.0f;
-        if (m <= kHitSlots) {
-            // odd-even transposition sort of the (entry, exit) pairs by entry
+        if (h.m <= kHitSlots) {
+            // Batcher's odd-even merge sort of the (entry, exit) pairs by entry
+            auto order = [&](int i, int j) {
+                const bool sw = h.a[j] < h.a[i];
+                const float ta = sw ? h.a[j] : h.a[i], tb = sw ? h.b[j] : h.b[i];
+                const float ua = sw ? h.a[i] : h.a[j], ub = sw ? h.b[i] : h.b[j];
+                h.a[i] = ta;
+                h.b[i] = tb;
+                h.a[j] = ua;
+                h.b[j] = ub;
+            };
 #pragma unroll
-            for (int pass = 0; pass < kHitSlots; ++pass)
+            for (int p = 1; p < kHitSlots; p *= 2)
 #pragma unroll
-                for (int j = pass & 1; j + 1 < kHitSlots; j += 2) {
-                    const bool sw = ca[j + 1] < ca[j];
-                    const float ta = sw ? ca[j + 1] : ca[j], tb = sw ? cb[j + 1] : cb[j];
-                    const float ua = sw ? ca[j] : ca[j + 1], ub = sw ? cb[j] : cb[j + 1];
-                    ca[j] = ta;
-                    cb[j] = tb;
-                    ca[j + 1] = ua;
-                    cb[j + 1] = ub;
-                }
-            float s0 = ca[0], e0 = cb[0];
+                for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+                    for (int j = k % p; j + k < kHitSlots; j += 2 * k)
+#pragma unroll
+                        for (int i = 0; i < k; ++i)
+                            if (i + j + k < kHitSlots && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order(i + j, i + j + k);
+            float s0 = h.a[0], e0 = h.b[0];
 #pragma unroll
             for (int j = 1; j < kHitSlots; ++j) {
-                if (j < m) {
-                    if (ca[j] <= e0) {
-                        e0 = __builtin_fmaxf(e0, cb[j]);
+                if (j < h.m) {
+                    if (h.a[j] <= e0) {
+                        e0 = __builtin_fmaxf(e0, h.b[j]);
                     } else {
                         acc += e0 - s0;
-                        s0 = ca[j];
-                        e0 = cb[j];
+                        s0 = h.a[j];
+                        e0 = h.b[j];
                     }
                 }
             }
-            if (m > 0) acc += e0 - s0;
+            if (h.m > 0) acc += e0 - s0;
         } else {
             float t = 0.0f;
             for (int k = 0; k < n && t < dist; ++k) {
@@ -957,15 +996,13 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         // traced there too, with the path's next ray
         bool nee_now = false, ray_now = false;
         V3 nee_x = v3(0, 0, 0), nee_d = v3(0, 0, 1);
-        if (state == S_FLY) {
-            // one Philox block per flight; the boundary query (the medium
-            // piece of the ray containing or following t) is skipped when the
-            // flight is shorter than the conservative radius at its start
-            const uint4 w = rng.block(c0++);
-            const float l = -flight_ln(u01(w.x)) * A.inv_sigma_t;
-            float ps = t, pe = INFINITY;
-            bool inside = l < G.flight_bound(A, fma3(t, d, o));
-            if (!inside && !G.piece(o, d, t, ps, pe)) {
+        // one Philox block per flight; the boundary query (the medium piece of
+        // the ray containing or following t) is skipped when the flight is
+        // shorter than the conservative radius at its start
+        uint4 w = make_uint4(0, 0, 0, 0);
+        float l = 0.0f, ps = t, pe = INFINITY;
+        auto end_flight = [&](bool found) __attribute__((always_inline)) {
+            if (!found) {
                 path_end = true;
             } else {
                 t = __builtin_fmaxf(t, ps);
@@ -1056,6 +1093,19 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     }
                 }
             }
+        };
+        bool near = true;
+        if (state == S_FLY) {
+            w = rng.block(c0++);
+            l = -flight_ln(u01(w.x)) * A.inv_sigma_t;
+            near = l < G.flight_bound(A, fma3(t, d, o));
+            if constexpr (!kWaveLight) end_flight(near || G.piece(o, d, t, ps, pe));
+        }
+        if constexpr (kWaveLight) {
+            const bool need = state == S_FLY && !near;
+            if (need) T.dir[lane_id()] = make_float4(d.x, d.y, d.z, 0.0f);
+            const bool found = G.wave_piece(T.pos, T.flight, T.dir, need, o, lane_id(), t, ps, pe);
+            if (state == S_FLY) end_flight(found);
         }
 
         if constexpr (kWaveLight) {
@@ -1361,10 +1411,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 wave_sync();
                 // A flight of the ray (o, d) from t: its end in t; 0 in the
                 // medium, 1 at the boundary, 2 if the ray leaves for good.
-                auto flight = [&](V3 fo, V3 fd, float& ft, float l) __attribute__((always_inline)) -> int {
-                    float ps = ft, pe = INFINITY;
-                    const bool inside = l < G.flight_bound(A, fma3(ft, fd, fo));
-                    if (!inside && !G.piece(fo, fd, ft, ps, pe)) return 2;
+                auto fly = [&](bool found, float ps, float pe, float& ft, float l) __attribute__((always_inline)) -> int {
+                    if (!found) return 2;
                     ft = __builtin_fmaxf(ft, ps);
                     if (ft + l >= pe) {
                         ft = pe;
@@ -1385,7 +1433,10 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                         const int at = slot0 + (int)e0;
                         if (p_ev + p_st == 0u) G.set_camera_ray(o, d);
                         else G.set_ray(o, d);
-                        const int out = flight(o, d, t, T.flight[at]);
+                        const float l = T.flight[at];
+                        float ps = t, pe = INFINITY;
+                        const bool found = l < G.flight_bound(A, fma3(t, d, o)) || G.piece(o, d, t, ps, pe);
+                        const int out = fly(found, ps, pe, t, l);
                         if (out == 2) {
                             ended = true;
                         } else if (out == 0) {
@@ -1470,8 +1521,17 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     light = G.light_and_ray(A, S, followed || T.light[slot0 + mine] != 0.0f, p_mine, d_mine, followed,
                                             o_mine, d_mine);
                 else if (followed) G.set_ray(o_mine, d_mine);
+                bool found = true;
+                float ps = 0.0f, pe = INFINITY;
                 if (followed) {
-                    out = flight(o_mine, d_mine, t_mine, l_mine);
+                    found = l_mine < G.flight_bound(A, o_mine);
+                    if constexpr (!kWaveLight) found = found || G.piece(o_mine, d_mine, 0.0f, ps, pe);
+                }
+                // (the draws in LDS have served)
+                if constexpr (kWaveLight)
+                    found = G.wave_piece(T.turn, T.flight, T.dir, !found, o_mine, slot0 + mine, 0.0f, ps, pe);
+                if (followed) {
+                    out = fly(found, ps, pe, t_mine, l_mine);
                     // it began outside the body by a rounding
                     if (out == 0 && t_mine != l_mine) out = 3;
                     if (kSteps && out == 0) r_mine = __builtin_fminf(G.radius(A, p_mine), A.r_cap);

@@ -632,3 +632,25 @@ def test_learned_paths_traced_together_are_the_same(msst, oracle, name, sigma_t,
     for k in wide:
         assert torch.equal(wide[k], spread[k]), (k, int((wide[k] != spread[k]).sum()))
     assert int(wide["counters"][2]) > 100
+
+
+@pytest.mark.parametrize("n", [6, 63, 150])
+def test_overlapping_spheres_and_boxes_path_by_path(msst, oracle, n):
+    """Rays through more overlapping spheres and boxes than a lane keeps hits,
+    with one ray and up to all of a wave's at a time sharing the primitives
+    out: against the oracle (bounds as for many spheres), and the same for any
+    number of rays at a time, bit for bit."""
+    announce(f"render {n} overlapping spheres and boxes")
+    rng = np.random.default_rng(n)
+    c = rng.uniform(-0.5, 0.5, (n, 3))
+    prims = np.array([W.prim_sphere(c[i], rng.uniform(0.2, 0.5)) if i % 3 else W.prim_box(c[i], rng.uniform(0.1, 0.4, 3))
+                      for i in range(n)], np.float32)
+    cam, light, med = f32_camera(W.camera_c5(40, 30)), f32_light(W.light_c5()), f32_medium(W.medium_c5())
+    r = msst.Renderer(prims, cam, light)
+    wide = r.render(med, method=PLAIN, spp=1, seed=29, blocks_per_cu=1, chunk=1)
+    one = r.render(med, method=PLAIN, spp=1, seed=29, blocks_per_cu=64, chunk=1)
+    for k in wide:
+        assert torch.equal(wide[k], one[k]), k
+    o = oracle.render(oracle.Scene(prims), cam, light, med, method=oracle.METHOD_PLAIN_NEE, spp=1, seed=29)
+    frac, _ = compare_paths({k: v.cpu().numpy() for k, v in wide.items()}, o, rel=LEARNED_REL)
+    assert frac < 4e-3 and o["events"].sum() > 1000
