@@ -317,7 +317,15 @@ constexpr int kHitSlots = 8;
 // moves; comparing the count with each slot took half as many again.)
 struct Hits {
     float a[kHitSlots], b[kHitSlots];
-    int m = 0;
+    int m;
+    __device__ __forceinline__ void clear(float none) {
+#pragma unroll
+        for (int j = 0; j < kHitSlots; ++j) {
+            a[j] = INFINITY;
+            b[j] = none;
+        }
+        m = 0;
+    }
     __device__ __forceinline__ void add(float ta, float tb) {
 #pragma unroll
         for (int j = kHitSlots - 1; j > 0; --j) {
@@ -352,8 +360,7 @@ struct GeoMany {
     // are this lane's; the `step` lanes that share a ray are neighbours.
     __device__ __forceinline__ void piece_of(V3 o, V3 d, float t, int first, int step, float& s, float& e) const {
         Hits h;
-#pragma unroll
-        for (int j = 0; j < kHitSlots; ++j) h.a[j] = INFINITY, h.b[j] = -INFINITY;
+        h.clear(-INFINITY);
         s = INFINITY;
         for (int i = first; i < n; i += step) {
             float a, b;
@@ -467,31 +474,23 @@ struct GeoMany {
     }
     __device__ __forceinline__ static bool active_any(float lo0) { return lo0 != INFINITY; }
 
-    // Shadow ray: the primitives (all of them, or those of a wave mask)
-    // contribute their hit intervals clipped to [0, dist] (8 slots), a
-    // sorting network orders them by entry and a sweep adds the length of
-    // their union; more than 8 hits falls back to piece-by-piece queries.
-    __device__ __forceinline__ float light(const RenderArgs& A, V3 x, V3 d) const { return light_masked(A, x, d, nullptr); }
-    __device__ __forceinline__ float light_masked(const RenderArgs& A, V3 x, V3 d, const uint64_t* mask) const {
-        V3 wl = v3(A.light[0] - x.x, A.light[1] - x.y, A.light[2] - x.z);
+    // Shadow ray: the primitives contribute their hit intervals clipped to
+    // [0, dist] (8 slots), a sorting network orders them by entry and a sweep
+    // adds the length of their union; more than 8 hits falls back to
+    // piece-by-piece queries.
+    __device__ __forceinline__ static V3 to_light(const RenderArgs& A, V3 x, float& dist, float& inv_dist) {
+        const V3 wl = v3(A.light[0] - x.x, A.light[1] - x.y, A.light[2] - x.z);
         const float dist2 = dot(wl, wl);
-        const float inv_dist = fast_rsq(dist2);
-        const float dist = dist2 * inv_dist;
-        wl = inv_dist * wl;
-        Hits h;
-#pragma unroll
-        for (int j = 0; j < kHitSlots; ++j) h.a[j] = h.b[j] = INFINITY;
-        auto visit = [&](int i) {
-            float a, b;
-            if (prim_interval(prim + 8 * i, x, wl, a, b) && b > 0.0f && a < dist)
-                h.add(__builtin_fmaxf(a, 0.0f), __builtin_fminf(b, dist));
-        };
-        if (mask == nullptr) {
-            for (int i = 0; i < n; ++i) visit(i);
-        } else {
-            for (int k = 0; k < kMaxManyPrims / 64; ++k)
-                for (uint64_t bits = mask[k]; bits != 0; bits &= bits - 1) visit(64 * k + __builtin_ctzll(bits));
-        }
+        inv_dist = fast_rsq(dist2);
+        dist = dist2 * inv_dist;
+        return inv_dist * wl;
+    }
+    __device__ __forceinline__ void visit(int i, V3 x, V3 wl, float dist, Hits& h) const {
+        float a, b;
+        if (prim_interval(prim + 8 * i, x, wl, a, b) && b > 0.0f && a < dist)
+            h.add(__builtin_fmaxf(a, 0.0f), __builtin_fminf(b, dist));
+    }
+    __device__ __forceinline__ float length_inside(Hits& h, V3 x, V3 wl, float dist) const {
         float acc = 0.0f;
         if (h.m <= kHitSlots) {
             // Batcher's odd-even merge sort of the (entry, exit) pairs by entry
@@ -535,6 +534,80 @@ struct GeoMany {
                 acc += __builtin_fminf(pe, dist) - ps;
                 t = pe;
             }
+        }
+        return acc;
+    }
+    __device__ __forceinline__ float light(const RenderArgs& A, V3 x, V3 d) const {
+        float dist, inv_dist;
+        const V3 wl = to_light(A, x, dist, inv_dist);
+        Hits h;
+        h.clear(INFINITY);
+        for (int i = 0; i < n; ++i) visit(i, x, wl, dist, h);
+        const float acc = length_inside(h, x, wl, dist);
+        return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
+    }
+    // The same for the lanes in `active` of a converged wave, with the wave's
+    // mask.  Up to 32 shadow rays have 2, up to 16 have 4 and up to 8 have 8
+    // lanes each, which share the primitives; the first of them takes the
+    // others' hits over (more lanes hand over more than they save).  512^2 x 32
+    // of 64 spheres 41.1 -> 38.6 ms; with the shared loop for full waves too
+    // 44.9.
+    __device__ __forceinline__ float wave_light(const RenderArgs& A, bool active, V3 x, V3 d, const uint64_t* mask) const {
+        const uint64_t act = ballot(active);
+        if (act == 0) return 0.0f;
+        const int n_act = __popcll(act), lane = lane_id();
+        const int lg = n_act > 32 ? 0 : n_act > 16 ? 1 : n_act > 8 ? 2 : 3;
+        int first = lane, mine = 0, home = lane;
+        V3 xr = x;
+        bool ray = active;
+        if (lg > 0) {
+            // origins to the first lane of each ray (a lane without one sends
+            // its own to lane 1, which is not), then to all of its lanes
+            first = lane >> lg << lg;
+            mine = lane - first;
+            home = rank_in(act) << lg;
+            ray = (lane >> lg) < n_act;
+            const int to = 4 * (active ? home : 1);
+            auto give = [&](float v) __attribute__((always_inline)) {
+                return __shfl(__int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v))), first);
+            };
+            xr = v3(give(x.x), give(x.y), give(x.z));
+        }
+        float dist, inv_dist;
+        V3 wl = to_light(A, xr, dist, inv_dist);
+        Hits h;
+        h.clear(INFINITY);
+        if (lg == 0) {
+            if (ray)
+                for (int k = 0; k < kMaxManyPrims / 64; ++k)
+                    for (uint64_t bits = mask[k]; bits != 0; bits &= bits - 1) visit(64 * k + __builtin_ctzll(bits), xr, wl, dist, h);
+        } else if (ray) {
+            for (int k = 0; k < kMaxManyPrims / 64; ++k)
+                for (uint64_t bits = mask[k]; bits != 0;) {
+                    int i = -1;
+                    for (int g = 0; g < 1 << lg && bits != 0; ++g) {
+                        if (g == mine) i = 64 * k + __builtin_ctzll(bits);
+                        bits &= bits - 1;
+                    }
+                    if (i >= 0) visit(i, xr, wl, dist, h);
+                }
+        }
+        for (int g = 1; g < 1 << lg; ++g) {
+            const int from = (lane + g) & 63;
+            const int m = __shfl(h.m, from);
+#pragma unroll
+            for (int j = 0; j < kHitSlots; ++j) {
+                if (ballot(mine == 0 && j < m) == 0) break;
+                const float ta = __shfl(h.a[j], from), tb = __shfl(h.b[j], from);
+                if (mine == 0 && j < m) h.add(ta, tb);
+            }
+            if (mine == 0 && m > kHitSlots) h.m += m - kHitSlots;
+        }
+        float acc = 0.0f;
+        if (ray && mine == 0) acc = length_inside(h, xr, wl, dist);
+        if (lg > 0) {
+            acc = __shfl(acc, home);
+            wl = to_light(A, x, dist, inv_dist);
         }
         return A.intensity * hg_eval(cold_hg(), dot(d, wl)) * fast_exp(-A.sigma_t * acc) * (inv_dist * inv_dist);
     }
@@ -788,12 +861,11 @@ __device__ __forceinline__ void stage_normals(const RenderArgs& A, const PackedM
 }
 
 // Runs one decoder over the first n compacted rows (16-path MFMA tiles);
-// each row's (mean, log variance) outputs overwrite its inputs.  FRESH: the
-// weights' addresses are made here, not held in registers through the flights.
-template <bool FRESH>
+// each row's (mean, log variance) outputs overwrite its inputs.  The weights'
+// addresses are made here, not held in registers through the flights.
 __device__ __forceinline__ void decode_tiles(const PackedModel* pm, RenderLds& L, int n) {
     wave_sync();
-    if (FRESH) asm volatile("" : "+s"(pm));
+    asm volatile("" : "+s"(pm));
     const int n_tiles = (n + 15) >> 4;
     if (pm->n_linear == kDecLayers) {
         const DecoderRegs w = load_decoder(pm);
@@ -829,10 +901,10 @@ __device__ __forceinline__ void read_row(const PackedModel* pm, const RenderLds&
 }
 
 // decode_tiles, then the sample of row `slot` for lanes that staged one.
-template <bool FRESH, int PO>
+template <int PO>
 __device__ __forceinline__ void decode_rows(const PackedModel* pm, RenderLds& L, bool mine, int slot, int n,
                                             float* y) {
-    decode_tiles<FRESH>(pm, L, n);
+    decode_tiles(pm, L, n);
     if (mine) read_row<PO>(pm, L, slot, y);
     wave_sync();
 }
@@ -1111,7 +1183,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         if constexpr (kWaveLight) {
             uint64_t mk[kMaxManyPrims / 64];
             G.light_mask(A, nee_now, nee_x, mk);
-            if (nee_now) Lp += A.albedo * G.light_masked(A, nee_x, nee_d, mk);
+            const float li = G.wave_light(A, nee_now, nee_x, nee_d, mk);
+            if (nee_now) Lp += A.albedo * li;
         }
         if constexpr (kPairs) {
             const float li = G.light_and_ray(A, S, nee_now, nee_x, nee_d, ray_now, o, d);
@@ -1130,12 +1203,10 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         // What follows from these alone, and the weights' addresses, is worked
         // out here: held through the flights it cost the kernels of few
         // primitives 17 spilled registers (the learned 512^2 x 256 image 15.1
-        // ms, so 14.5).  The many-sphere kernels, whose state is in LDS, are
-        // the faster for holding it (53.4 ms, so 55.0).
-        constexpr bool kFresh = !kWaveLight;
+        // ms, so 14.5; 64 spheres 39.1, so 38.6).
         float albedo = A.albedo;
         int nee_chain = A.nee_chain;
-        if (kFresh) asm volatile("" : "+s"(albedo), "+s"(nee_chain));
+        asm volatile("" : "+s"(albedo), "+s"(nee_chain));
         const int n_wait = __popcll(wmask);
         float y[6];
         float N = 1.0f, psi = 0.0f;
@@ -1147,7 +1218,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             stage_row<1, 2>(A.pm[0], L, slot0, prng, pc0, c2);
         }
         stage_normals<1>(A, A.pm[0], L, n_wait);
-        decode_rows<kFresh, 1>(A.pm[0], L, mine, slot0, n_wait, y);
+        decode_rows<1>(A.pm[0], L, mine, slot0, n_wait, y);
         bool alive = false;
         float u_hg = 0.5f, u_first = 1.0f, phiN = 1.0f;
         if (mine) {
@@ -1203,7 +1274,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 stage_row<3, 3>(A.pm[1], L, row, prng, pc0, c3);
             }
             stage_normals<3>(A, A.pm[1], L, __popcll(pmask));
-            decode_rows<kFresh, 3>(A.pm[1], L, use_path, row, __popcll(pmask), y);
+            decode_rows<3>(A.pm[1], L, use_path, row, __popcll(pmask), y);
             if (use_path) {
                 ct = __builtin_fminf(1.0f, __builtin_fmaxf(-1.0f, y[0]));
                 al = y[1];
@@ -1267,7 +1338,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                     if ((evbits >> (k - ka)) & 1u) stage_row<6, 7>(A.pm[2], L, base + j++, prng, c, c7);
                 }
                 stage_normals<6>(A, A.pm[2], L, n_rows);
-                decode_tiles<kFresh>(A.pm[2], L, n_rows);
+                decode_tiles(A.pm[2], L, n_rows);
             }
             int j = 0;
             for (int k = ka; k < kb; ++k) {
@@ -1294,7 +1365,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 if constexpr (kWaveLight) {
                     uint64_t mk[kMaxManyPrims / 64];
                     G.light_mask(A, lit_k, Xw, mk);
-                    if (lit_k) pLp += w_nee * G.light_masked(A, Xw, Ww, mk);
+                    const float li = G.wave_light(A, lit_k, Xw, Ww, mk);
+                    if (lit_k) pLp += w_nee * li;
                 }
             }
             wave_sync();
@@ -1551,7 +1623,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 if constexpr (kWaveLight) {
                     uint64_t mk[kMaxManyPrims / 64];
                     G.light_mask(A, lit, p_mine, mk);
-                    if (lit) light = G.light_masked(A, p_mine, d_mine, mk);
+                    const float li = G.wave_light(A, lit, p_mine, d_mine, mk);
+                    if (lit) light = li;
                 } else if constexpr (kPairs) {
                     if (!lit) light = 0.0f;
                 } else {
