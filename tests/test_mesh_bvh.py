@@ -85,3 +85,76 @@ def test_stackless_traversal_reaches_every_crossed_triangle(msst):
             k = k + 1 if (hit and i[k, 7] < 0) else i[k, 3]
         assert got == want
         assert len(want) % 2 == 0
+
+
+def reference_bvh(tris):
+    """The documented construction, split by split in float32: nodes as
+    (lo, hi, skip, leaf) in preorder and the triangles' order."""
+    f32 = np.float32
+    v = tris.reshape(-1, 3, 3)
+
+    def fold(rows, better, start):
+        out = np.full(3, start, f32)
+        for r in rows:
+            out = np.where(better(r, out), r, out)  # the earlier of equal values
+        return out
+
+    def area(lo, hi):
+        dx, dy, dz = (float(x) for x in (hi - lo))
+        return 0.0 if dx < 0 else dx * dy + dy * dz + dz * dx
+
+    nodes = []
+
+    def build(ids):
+        self = len(nodes)
+        nodes.append(None)
+        pts = v[ids].reshape(-1, 3)
+        lo, hi = fold(pts, np.less, np.inf), fold(pts, np.greater, -np.inf)
+        if len(ids) <= 4:
+            nodes[self] = (lo, hi, self + 1, (build.first << 4) | len(ids))
+            build.first += len(ids)
+            return list(ids)
+        mid = ((v[ids, 0] + v[ids, 1]) + v[ids, 2]) / f32(3)
+        clo, chi = mid.min(0), mid.max(0)
+        best = (np.inf, None, None)
+        for a in range(3):
+            if not chi[a] - clo[a] > 0:
+                continue
+            k = np.clip(((mid[:, a] - clo[a]) / (chi[a] - clo[a]) * f32(16)).astype(np.int64), 0, 15)
+            for split in range(1, 16):
+                left = k < split
+                if left.all() or not left.any():
+                    continue
+                sides = [v[ids[m]].reshape(-1, 3) for m in (left, ~left)]
+                cost = sum(area(p.min(0), p.max(0)) * (len(p) // 3) for p in sides)
+                if cost < best[0]:
+                    best = (cost, left, a)
+        assert best[1] is not None, "a median split has no fixed order"
+        order = build(ids[best[1]]) + build(ids[~best[1]])
+        nodes[self] = (lo, hi, len(nodes), -1)
+        return order
+
+    build.first = 0
+    return nodes, build(np.arange(len(v)))
+
+
+@pytest.mark.parametrize("kind", ["blob", "soup", "signed zeros"])
+@pytest.mark.parametrize("n", [1, 4, 5, 17, 200])
+def test_nodes_are_those_of_the_plain_construction(msst, kind, n):
+    """Bounds, links and the triangles' order byte for byte, signs of zeros
+    included (they depend on the order in which bounds are folded)."""
+    rng = np.random.default_rng(n)
+    if kind == "blob":
+        tris = W.mesh_blob(2, 3)[:n]
+    else:
+        tris = rng.normal(size=(n, 9))
+        if kind == "signed zeros":
+            tris = np.where(rng.random((n, 9)) < 0.5, np.copysign(0.0, tris), tris)
+    tris = np.ascontiguousarray(tris, np.float32)
+    ts, f, i = build(msst, tris)
+    nodes, order = reference_bvh(tris)
+    assert ts.tobytes() == tris[order].tobytes()
+    assert len(f) == len(nodes)
+    for k, (lo, hi, skip, leaf) in enumerate(nodes):
+        assert f[k, 0:3].tobytes() == lo.tobytes() and f[k, 4:7].tobytes() == hi.tobytes()
+        assert (i[k, 3], i[k, 7]) == (skip, leaf)
