@@ -688,14 +688,16 @@ struct GeoMesh {
     }
 
     // The shadow rays of the lanes in `lit`, from x with direction of flight d,
-    // and the next rays (o, nd) of those in `go`, which start there, traced by
-    // the whole wave: a lane begins with its own next ray, and lanes without a
-    // segment take the next shadow ray that has none.  Returns the light.  (One
-    // after the other the two traversals each ran as long as their longest ray,
-    // with 18 of 64 lanes at a node: a 256^2 x 128 image 37.0 ms, 29.3 so, 28.2
-    // with lanes that leave the nodes at three of eight busy.)
+    // and the next rays (o, nd) of those in `go`, from `inside` the body or from
+    // the camera, traced by the whole wave: a lane begins with its own next ray,
+    // and lanes without a segment take the next shadow ray that has none.
+    // Returns the light.  (One after the other the two traversals each ran as
+    // long as their longest ray, with 18 of 64 lanes at a node: a 256^2 x 128
+    // image 37.0 ms, 29.3 so, 28.0 with lanes that leave the nodes at three of
+    // eight busy, 27.1 with camera rays, and rays after learned steps, in this
+    // pass instead of passes of a few lanes each.)
     __device__ __forceinline__ float light_and_ray(const RenderArgs& A, PairLds& S, bool lit, V3 x, V3 d, bool go, V3 o,
-                                                   V3 nd) {
+                                                   V3 nd, bool inside) {
         const int lane = lane_id();
         const uint32_t n = (uint32_t)n_nodes;
         V3 wl = v3(A.light[0] - x.x, A.light[1] - x.y, A.light[2] - x.z);
@@ -718,7 +720,7 @@ struct GeoMesh {
         else w.m = w.leaf = 0, w.i = n;
         for (;;) {
             if (owner >= 0 && w.done(n)) {
-                if (owner < 64) set_intervals(w, true);
+                if (owner < 64) set_intervals(w, inside);
                 else S.length[owner - 64] = length_inside(w, w.thi);
                 owner = -1;
             }
@@ -948,6 +950,10 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
     // step (wave-uniform): a pass also runs once the oldest wait reaches
     // max_wait, so rare steps do not idle lanes for long
     int end_age = 0, wait_age = 0;
+    // meshes: a ray about o, along d, is due (from inside the body: after a
+    // learned step, or from the camera)
+    enum : int { kNoRay = 0, kInside, kCamera };
+    int due = kNoRay;
     // The lane's work unit (its accumulators, next sample, end of range and
     // index; U_NONE when it has none) and its totals of events, learned
     // steps and truncated paths for the launch counters live in LDS: touched
@@ -1055,7 +1061,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         if (start) {
             const uint32_t unit = tot[U_UNIT][tid];
             begin_path(udiv_exact(unit, (uint32_t)C->n_chunks, C->inv_n_chunks), s_next);
-            G.set_camera_ray(o, d);
+            if constexpr (kPairs) due = kCamera;
+            else G.set_camera_ray(o, d);
             tot[U_NEXT][tid] = (uint32_t)(s_next + 1);
         }
     };
@@ -1066,7 +1073,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         // many primitives: a plain event's shadow ray is traced after the
         // branch, where the whole wave builds its primitive mask; a mesh's is
         // traced there too, with the path's next ray
-        bool nee_now = false, ray_now = false;
+        bool nee_now = false;
         V3 nee_x = v3(0, 0, 0), nee_d = v3(0, 0, 1);
         // one Philox block per flight; the boundary query (the medium piece of
         // the ray containing or following t) is skipped when the flight is
@@ -1157,7 +1164,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                                 const HgSample h = hg_sample(cold_hg(), u01(w.y));
                                 d = scatter(d, h.mu, h.sin_t, u01(w.z));
                                 o = p;
-                                if constexpr (kPairs) ray_now = true;
+                                if constexpr (kPairs) due = kInside;
                                 else G.set_ray(o, d);
                                 t = 0.0f;
                             }
@@ -1167,7 +1174,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             }
         };
         bool near = true;
-        if (state == S_FLY) {
+        if (state == S_FLY && due == kNoRay) {
             w = rng.block(c0++);
             l = -flight_ln(u01(w.x)) * A.inv_sigma_t;
             near = l < G.flight_bound(A, fma3(t, d, o));
@@ -1187,8 +1194,9 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
             if (nee_now) Lp += A.albedo * li;
         }
         if constexpr (kPairs) {
-            const float li = G.light_and_ray(A, S, nee_now, nee_x, nee_d, ray_now, o, d);
+            const float li = G.light_and_ray(A, S, nee_now, nee_x, nee_d, due != kNoRay, o, d, due == kInside);
             if (nee_now) Lp += A.albedo * li;
+            due = kNoRay;
         }
     };
 
@@ -1390,7 +1398,8 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
         const bool alive = learned_core(wmask, mine, o, d, r_step, rng, c0, Lp, p_st);
         if (mine) {
             if (alive) {
-                G.set_ray(o, d);
+                if constexpr (kPairs) due = kInside;
+                else G.set_ray(o, d);
                 t = 0.0f;
                 state = S_FLY;
             } else {
@@ -1591,7 +1600,7 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
                 float light = 0.0f;
                 if constexpr (kPairs)
                     light = G.light_and_ray(A, S, followed || T.light[slot0 + mine] != 0.0f, p_mine, d_mine, followed,
-                                            o_mine, d_mine);
+                                            o_mine, d_mine, true);
                 else if (followed) G.set_ray(o_mine, d_mine);
                 bool found = true;
                 float ps = 0.0f, pe = INFINITY;
