@@ -5,6 +5,7 @@
 // and the FP16 distance grid of a mesh on the device.
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "host.hpp"
@@ -432,8 +433,12 @@ ms_status ms_build_mesh_bvh(const float* tris_host, int32_t n_tris, void* nodes_
     ms_mesh_bvh_size(n_tris, &need);
     if (node_bytes < need) return set_error(MS_ERR_WORKSPACE_TOO_SMALL, "ms_build_mesh_bvh: nodes need %zu bytes", need);
     Builder bld;
-    bld.init(tris_host, n_tris);
-    bld.build(0, n_tris, 0);
+    try {
+        bld.init(tris_host, n_tris);
+        bld.build(0, n_tris, 0);
+    } catch (const std::bad_alloc&) {
+        return set_error(MS_ERR_UNSUPPORTED, "ms_build_mesh_bvh: no host memory for %d triangles", n_tris);
+    }
     std::memcpy(nodes_host, bld.nodes.data(), bld.nodes.size() * sizeof(BvhNode));
     for (int i = 0; i < n_tris; ++i)
         std::memcpy(tris_sorted_host + 9 * (size_t)i, tris_host + 9 * (size_t)bld.idx[i], 9 * sizeof(float));
