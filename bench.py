@@ -45,18 +45,18 @@ ALG_PER_PATH = 200.0
 ALG_PER_EVENT = 350.0
 ALG_PER_STEP_ONE_EVENT = 2600.0
 ALG_PER_EXTRA_EVENT = 1000.0
-OPS_PER_PATH = 400.0         # counted: camera ray, primary intervals, banking the result
-OPS_PER_EVENT = 460.0        # counted: one plain collision
-OPS_PER_STEP = 5600.0        # counted: one learned step with one representative event
+OPS_PER_PATH = 404.0         # counted: camera ray, primary intervals, banking the result
+OPS_PER_EVENT = 436.0        # counted: one plain collision
+OPS_PER_STEP = 5050.0        # counted: one learned step with one representative event
 MFMA_FLOP_PER_STEP = 2944.0  # real decoder MACs x 2 (LengthGen + PathGen + EventGen)
-OPS_PER_WALK_EVENT = 186.0   # one walk event: Philox block, HG sample, scatter, flight, exit test
+OPS_PER_WALK_EVENT = 167.0   # counted: one walk event: Philox block, HG sample, scatter, flight, exit test
 PEAK_VALU_LANEOPS = 256 * 2.4e9 * 64   # 3.93e13 lane-op slots/s, non-packed FP32 VALU
 CALIB_ROWS = 8192  # training conditions that calibrate the FP8 activation scales
 PEAK_MFMA_BF16 = 2.5e15
 PEAK_HBM_BYTES = 8.0e12
 # active-lane VALU slots per decoded sample of cvae_sample for the standard
 # shapes (latent 4, width 16, three layers), (model, precision 1 BF16 / 2 FP8)
-SAMPLE_VALU_SLOTS = {(0, 1): 709.0, (0, 2): 793.0, (1, 1): 739.0, (1, 2): 823.0, (2, 1): 874.0, (2, 2): 958.0}
+SAMPLE_VALU_SLOTS = {(0, 1): 514.0, (0, 2): 694.0, (1, 1): 560.0, (1, 2): 740.0, (2, 1): 650.0, (2, 2): 830.0}
 
 
 def log(msg):

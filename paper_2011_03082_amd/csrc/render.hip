@@ -13,6 +13,9 @@
 //                 decoder inputs are compacted into 16-path tiles in LDS and
 //                 LengthGen, the absorption test, PathGen and EventGen run on
 //                 matrix cores for exactly those lanes.
+// The last paths of a wave, and those of small launches, are traced together,
+// several lanes to a path; boundary and shadow rays of meshes and of many
+// primitives are shared by a wave's lanes throughout.
 // Per-unit results go to a partial buffer and are reduced per pixel in a
 // fixed order, so images are bitwise reproducible.
 #include <math.h>
@@ -613,20 +616,20 @@ struct GeoMany {
     }
 };
 
-// A closed triangle mesh: the crossings ahead of each new ray's origin (BVH
-// traversal of the half-line) alternate exit / entry from a scattering
-// point inside the body and entry / exit from the camera; up to four medium
-// intervals are kept in registers.  Radii come from the distance grid;
-// shadow rays traverse their own segment to the light.
 // A wave's shadow rays and their lengths inside the body (by lane).
 struct PairLds {
     float4 from[64], to[64];
     float length[64];
 };
 
+// A closed triangle mesh: the crossings ahead of each new ray's origin (BVH
+// traversal of the half-line) alternate exit / entry from a scattering
+// point inside the body and entry / exit from the camera; up to four medium
+// intervals are kept in registers.  Radii come from the distance grid;
+// shadow rays traverse their own segment to the light.
 struct GeoMesh {
-    static constexpr bool kPairs = true;
-    static constexpr bool kWaveLight = false;  // shadow rays traverse the BVH per lane
+    static constexpr bool kPairs = true;       // a wave's shadow and next rays in one pass
+    static constexpr bool kWaveLight = false;
     const BvhNode* nodes;
     const float* tris;
     int n_nodes;
