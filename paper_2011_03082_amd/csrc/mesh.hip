@@ -208,7 +208,11 @@ __device__ __forceinline__ float tri_ray_radius(const float* t, V3 u, float r) {
 
 // Squared FP32 distance from p to a triangle (the nearest of its edges, or
 // its plane where p projects inside), and shape, the relative error of its
-// normal in units of the FP32 rounding.
+// normal in units of the FP32 rounding.  The edges are differences of exact
+// values, good to a rounding; what is left grows with |p - a|, which the
+// triangle's size bounds.  (The unit normal keeps its products in range: edges
+// too long for the square of their cross product give a shape of 0 with a
+// distance of 0, or one that is not a number.)
 __device__ __forceinline__ float edge_dist2(V3 p, V3 e, float ee) {
     const float s = __builtin_fminf(1.0f, __builtin_fmaxf(0.0f, dot(p, e) * fast_rcp(ee)));
     const V3 q = p - s * e;
@@ -216,14 +220,15 @@ __device__ __forceinline__ float edge_dist2(V3 p, V3 e, float ee) {
 }
 __device__ __forceinline__ float tri_distance32(const float* t, V3 p, float& shape) {
     const V3 a = v3(t[0], t[1], t[2]), b = v3(t[3], t[4], t[5]), c = v3(t[6], t[7], t[8]);
-    const V3 e1 = b - a, e2 = c - b, e3 = a - c, nv = cross(e1, e2);
-    const float l1 = dot(e1, e1), l2 = dot(e2, e2), l3 = dot(e3, e3), nn = dot(nv, nv);
+    const V3 e1 = b - a, e2 = c - b, e3 = a - c, cr = cross(e1, e2);
+    const float l1 = dot(e1, e1), l2 = dot(e2, e2), l3 = dot(e3, e3), inv = fast_rsq(dot(cr, cr));
+    const V3 nv = inv * cr;
     const V3 pa = p - a, pb = p - b, pc = p - c;
     float d2 = __builtin_fminf(edge_dist2(pa, e1, l1), __builtin_fminf(edge_dist2(pb, e2, l2), edge_dist2(pc, e3, l3)));
     const bool in = dot(cross(e1, nv), pa) <= 0.0f && dot(cross(e2, nv), pb) <= 0.0f && dot(cross(e3, nv), pc) <= 0.0f;
     const float h = dot(nv, pa);
-    d2 = in ? __builtin_fminf(d2, h * h * fast_rcp(nn)) : d2;
-    shape = (l1 + l2 + l3) * fast_rsq(nn);
+    d2 = in ? __builtin_fminf(d2, h * h) : d2;
+    shape = (l1 + l2 + l3) * inv;
     return d2;
 }
 
@@ -268,14 +273,16 @@ __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float
                          (float)(loz + (bk + 0.5 * kBrick) * hz));
         // A centroid's distance from the brick's centre, the smallest of all
         // or of every fourth triangle: no voxel is farther than that plus
-        // r_brick from the mesh.
+        // r_brick from the mesh.  (A centroid is off by up to 4e-7 of its
+        // triangle's size, however near it is: 1e-6 of the radius is added to
+        // its distance, here and below.)
         const int stride = n_tris >= 4 * kGridThreads ? 4 : 1;
         float near = INFINITY;
         for (int q = stride * threadIdx.x; q < n_tris; q += stride * kGridThreads) {
             V3 m;
             float r;
             tri_sphere(tris + 9 * (int64_t)q, m, r);
-            if (r < INFINITY) near = __builtin_fminf(near, dot(m - cb, m - cb));
+            near = __builtin_fminf(near, __builtin_fmaf(1e-6f, r, fast_sqrt(dot(m - cb, m - cb))));
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) near = __builtin_fminf(near, __shfl_xor(near, off));
@@ -283,7 +290,6 @@ __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < kGridWaves; ++w) near = __builtin_fminf(near, near_w[w]);
-        near = fast_sqrt(near);
 
         // Lists the triangles from `first` on that pass the brick's tests;
         // returns where the next part starts (n_tris: all done).
@@ -343,8 +349,7 @@ __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float
             for (int e = wave; e < n_dist; e += kGridWaves) {
                 const float4 s = list_s[e];
                 const V3 v = v3(s.x, s.y, s.z) - p;
-                const float d2 = dot(v, v);
-                bound = s.w < INFINITY ? __builtin_fminf(bound, d2) : bound;
+                bound = __builtin_fminf(bound, __builtin_fmaf(1e-6f, s.w, fast_sqrt(dot(v, v))));
             }
             for (int e = wave; e < n_ray; e += kGridWaves) {
                 const float4 s = list_s[kGridList - 1 - e];
@@ -355,7 +360,7 @@ __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float
             }
             one_part = first == 0 && next == n_tris;
         }
-        bound_w[wave][lane] = fast_sqrt(bound);
+        bound_w[wave][lane] = bound;
         const uint64_t mask = ballot(odd);
         if (lane == 0) odd_w[wave] = mask;
         __syncthreads();
@@ -377,7 +382,7 @@ __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float
                 if (s.w < INFINITY) {
                     float shape;
                     const float d2 = tri_distance32(t, p, shape);
-                    const float most = bound + 1e-6f * (8.0f + shape) * (scale + bound);
+                    const float most = bound + 1e-6f * (8.0f + shape) * (scale + bound + s.w);
                     need = need && !(d2 > most * most);
                     if (ballot(need) == 0) continue;
                 }

@@ -92,3 +92,45 @@ def test_mesh_grid_culling_matches_oracle(msst, oracle, name, res):
     g = msst.build_sdf_grid(None, res, LO, HI, tris=tris).cpu().numpy().view(np.uint16)
     o = oracle.Scene(None, tris=tris).build_grid(res, LO, HI)
     assert np.array_equal(g, o), (int((g != o).sum()), g.size)
+
+
+def sheets_beside_large_triangles(seed, size):
+    """Three triangles of `size`, their centroids within the grid, each with a
+    finely tessellated sheet 2e-8 of its size beside its plane: on one side of
+    the pair the large triangle is the nearest by less than FP32 resolves at
+    its vertices."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for _ in range(3):
+        q = np.linalg.qr(rng.normal(size=(3, 3)))[0]
+        ang = rng.uniform(0, 2 * np.pi) + np.arange(3) * 2 * np.pi / 3
+        big = (rng.uniform(-0.5, 0.5, 3) + size * (np.cos(ang)[:, None] * q[0] + np.sin(ang)[:, None] * q[1])).astype(np.float32)
+        v = big.astype(np.float64)
+        nrm = np.cross(v[1] - v[0], v[2] - v[0])
+        nrm /= np.linalg.norm(nrm)
+        e = v[1] - v[0]
+        e /= np.linalg.norm(e)
+        f = np.cross(nrm, e)
+        u = np.linspace(-0.8, 0.8, 21)
+        p = (v.mean(0) + 2e-8 * size * nrm + u[:, None, None] * e + u[None, :, None] * f).astype(np.float32)
+        quads = p[:-1, :-1], p[1:, :-1], p[1:, 1:], p[:-1, 1:]
+        out += [big.reshape(1, 9)]
+        for k in ((0, 1, 2), (0, 2, 3)):
+            out.append(np.concatenate([quads[j] for j in k], -1).reshape(-1, 9))
+    return np.concatenate(out)
+
+
+@pytest.mark.parametrize("size", [1e2, 1e3, 1e4, 1e6])
+def test_mesh_grid_beside_large_triangles_matches_oracle(msst, oracle, size):
+    """Triangles that reach far beyond the grid: their FP32 centroids and
+    distances are off by their vertices' rounding, which must neither drop a
+    triangle nor bound the distance too tightly.  As above both sides evaluate
+    the same FP64 distances; their rounding (1e-16 of the size, 1e-10 at most)
+    straddles a binary16 step (6e-5 or more at the distances of all but a
+    hundredth of the voxels) for one voxel in 10^6."""
+    announce(f"mesh sdf grid beside triangles of {size:g}")
+    tris = sheets_beside_large_triangles(int(size) % 97, size)
+    g = msst.build_sdf_grid(None, 20, LO, HI, tris=tris).cpu().numpy().view(np.uint16)
+    o = oracle.Scene(None, tris=tris).build_grid(20, LO, HI)
+    d = np.abs(g.view(np.float16).astype(np.float64)) - np.abs(o.view(np.float16).astype(np.float64))
+    assert np.array_equal(g, o), (int((g != o).sum()), g.size, float(d.max()))
