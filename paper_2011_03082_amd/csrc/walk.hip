@@ -266,7 +266,10 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
                 const float az = u01(w.z);
                 float l = -flight_ln(u01(w.x)) * inv_st, u = 0.0f;
                 if (MODE == MS_WALK_ANALOG) {
-                    if (active && u24(w.w) > a.surv_thr) l = INFINITY;
+                    // the flight of a survivor is finite, so that infinity
+                    // means absorbed alone (a medium can be as good as empty:
+                    // its photons leave, however far they would have flown)
+                    l = active && u24(w.w) > a.surv_thr ? INFINITY : __builtin_fminf(l, 0x1.fffffep127f);
                 } else if (uniform) {
                     u = (uint64_t)u24(w.w) * (nev + mine + 1u) <= (1ull << 24) ? 0.0f : INFINITY;
                 } else {

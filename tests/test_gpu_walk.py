@@ -197,3 +197,17 @@ def test_chains_walked_together_are_the_same(msst, kw):
         assert c[0] == part["n_scatter"].astype(np.int64).sum() and c[3] == part["n_scatter"].max()
         assert c[1] == part["absorbed"].sum() and c[2] == part["truncated"].sum()
         at += n
+
+
+@pytest.mark.parametrize("sigma_t,albedo", [(1e-46, 1.0), (1e-39, 0.5), (2e-38, 1.0), (2e-38, 0.5)])
+@pytest.mark.parametrize("n", [20, 700, 33000])
+def test_flights_too_long_for_a_float_leave(msst, oracle, sigma_t, albedo, n):
+    """A medium as good as empty: a flight's length, or the mean free path
+    itself, is infinite in FP32.  Such a photon leaves the sphere; only the
+    survival test absorbs (in a wave's last chains as in full waves)."""
+    announce(f"walk sigma_t={sigma_t:g} albedo={albedo} n={n}")
+    g, o, same = analog_parity(msst, oracle, n, seed=8, sigma_t=sigma_t, g=0.8, albedo=albedo, radius=1.5)
+    assert same.all(), int((~same).sum())
+    assert rel_err(g["exit_pos"], o["exit_pos"]).max() <= REL_TOL
+    assert rel_err(g["exit_dir"], o["exit_dir"]).max() <= REL_TOL
+    assert g["counters"][1] == o["absorbed"].sum()
