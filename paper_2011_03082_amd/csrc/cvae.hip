@@ -1007,8 +1007,8 @@ constexpr int kSampleWaves = 4;
 template <int T>
 struct SampleLds {
     static constexpr int kRows = 64 / T;
-    float x[kTile * T][kRows + 4];
-    float eps[kTile / 2 * T][kRows + 4];
+    static constexpr int kEps = kTile * T;
+    float x[kEps + kTile / 2 * T][kRows + 4];  // inputs, then normals from kEps on
 };
 
 // T: tiles per layer dimension of the packed model (pm->blocks).  Bound by
@@ -1023,7 +1023,7 @@ struct SampleLds {
 template <int T>
 __device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* cond, int64_t n, uint64_t seed,
                                             uint64_t id_offset, float* out, SampleLds<T>& L) {
-    constexpr int R = SampleLds<T>::kRows, kCond = kTile / T, kOut = kTile / 2;
+    constexpr int R = SampleLds<T>::kRows, kEps = SampleLds<T>::kEps, kCond = kTile / T, kOut = kTile / 2;
     const ConstModel c = (ConstModel)pm;
     const int P = c->p_out, Lt = c->latent, C = c->p_in;
     // this lane's row of a chunk; of a row's T lanes it takes every T-th
@@ -1055,7 +1055,7 @@ __device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* 
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int e = 4 * j + q;
-                if (e < Lt + P) L.x[e < Lt ? e : e + (kTile * T - Lt)][row] = nv[q];
+                if (e < Lt + P) L.x[e < Lt ? e : e + (kEps - Lt)][row] = nv[q];
             }
         }
 #pragma unroll
@@ -1063,7 +1063,7 @@ __device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* 
             const int k = q * T + part;
             if (k < C) L.x[Lt + k][row] = (cv[q] - c->mean_c[k]) * c->inv_std_c[k];
         }
-        for (int q = Lt + C + part; q < kTile * T; q += T) L.x[q][row] = 0.0f;
+        for (int q = Lt + C + part; q < kEps; q += T) L.x[q][row] = 0.0f;
         wave_sync();
         // each lane overwrites exactly the values that it read
         auto load = [&](int path, int f0) {
@@ -1099,7 +1099,7 @@ __device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* 
             for (int q = 0; q < kOut; ++q) {
                 const int k = q * T + part;
                 if (k >= P) break;
-                const float y = __builtin_fmaf(fast_exp(0.5f * clamp_lv(L.x[P + k][row])), L.eps[k][row], L.x[k][row]);
+                const float y = __builtin_fmaf(fast_exp(0.5f * clamp_lv(L.x[P + k][row])), L.x[kEps + k][row], L.x[k][row]);
                 out[i * P + k] = __builtin_fmaf(y, c->std_y[k], c->mean_y[k]);
             }
         }

@@ -449,3 +449,29 @@ def test_samples_of_few_rows(msst, oracle, model, width, latent, n_linear, preci
             assert np.median(err) < (1e-4 if precision == 1 else 1e-3) and err.max() < (0.1 if precision == 1 else 0.4)
         else:
             np.testing.assert_array_equal(rows, first[:n])
+
+
+@pytest.mark.parametrize("precision", [1, 2])
+@pytest.mark.parametrize("p_in,p_out,latent,width", [(8, 8, 8, 16), (12, 4, 1, 16), (1, 8, 8, 5), (16, 16, 16, 32),
+                                                     (1, 16, 1, 32), (16, 1, 16, 17)])
+def test_samples_of_the_largest_shapes(msst, oracle, p_in, p_out, latent, width, precision):
+    """Decoders that fill one tile or two with inputs and with outputs, up to
+    the last row of the posterior's normals: bounds as for a few rows (a
+    flipped rounding, one conversion in 2^16, is in fewer than half of them)."""
+    announce(f"cvae sample shape {p_in} {p_out} {latent} {width} precision={precision}")
+    shape = dict(model=2, p_in=p_in, p_out=p_out, latent=latent, width=width, n_linear=3)
+    master64 = oracle.cvae_init(shape, seed=7).astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(p_in + 100 * p_out)
+    stats = np.concatenate([rng.normal(size=16), rng.uniform(0.5, 1.5, 16), rng.normal(size=16), rng.uniform(0.5, 1.5, 16)])
+    packed = torch.empty(msst.cvae_packed_bytes(), dtype=torch.uint8, device="cuda")
+    msst.cvae_pack(shape, dev(master64), dev(stats, torch.float64), precision, packed)
+    n = 333
+    cond = rng.normal(size=(n, p_in)).astype(np.float32)
+    out = torch.full((n * p_out + 64,), 7.0, dtype=torch.float32, device="cuda")
+    msst.cvae_sample(packed, dev(cond), n, 3, 5, out)
+    got = out.cpu().numpy()
+    assert (got[n * p_out:] == 7.0).all()
+    ref = oracle.cvae_sample(shape, master64, stats, cond.astype(np.float64), 3, 5,
+                             precision=oracle.PREC_BF16 if precision == 1 else oracle.PREC_FP8)
+    err = np.abs(got[: n * p_out].reshape(n, p_out) - ref).max(axis=1) / stats[48:48 + p_out].max()
+    assert np.median(err) < (1e-4 if precision == 1 else 1e-3) and err.max() < (0.1 if precision == 1 else 0.4)
