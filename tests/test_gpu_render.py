@@ -654,3 +654,54 @@ def test_overlapping_spheres_and_boxes_path_by_path(msst, oracle, n):
     o = oracle.render(oracle.Scene(prims), cam, light, med, method=oracle.METHOD_PLAIN_NEE, spp=1, seed=29)
     frac, _ = compare_paths({k: v.cpu().numpy() for k, v in wide.items()}, o, rel=LEARNED_REL)
     assert frac < 4e-3 and o["events"].sum() > 1000
+
+
+@pytest.mark.parametrize("n", [6, 63, 150])
+def test_overlaps_in_full_waves(msst, oracle, n):
+    """The scenes above in an image large enough that one block per CU fills
+    its waves, a path per lane: each lane's boundary query and shadow ray
+    through more primitives than it keeps hits, up to 64 of them sharing a
+    wave.  Against the oracle (bounds as above), and bit for bit the same as
+    the launch that spreads the paths over eight lanes each, also with learned
+    steps."""
+    announce(f"render {n} overlapping spheres and boxes, full waves")
+    rng = np.random.default_rng(n)
+    c = rng.uniform(-0.5, 0.5, (n, 3))
+    prims = np.array([W.prim_sphere(c[i], rng.uniform(0.2, 0.5)) if i % 3 else W.prim_box(c[i], rng.uniform(0.1, 0.4, 3))
+                      for i in range(n)], np.float32)
+    w, h = 300, 240
+    # more units than a launch of half-filled waves holds at four waves a block
+    assert w * h > 32 * 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    cam, light, med = f32_camera(W.camera_c5(w, h)), f32_light(W.light_c5()), f32_medium(W.medium_c5())
+    r = msst.Renderer(prims, cam, light)
+    packed = pack_all(msst, models_for_test(oracle)[1])
+    for kw in (dict(method=PLAIN), dict(method=ST, sampler=CVAE, packed=packed, tau_min=3.0, nee_samples=2)):
+        full = r.render(med, spp=1, seed=29, blocks_per_cu=1, chunk=1, **kw)
+        spread = r.render(med, spp=1, seed=29, blocks_per_cu=64, chunk=1, **kw)
+        for k in full:
+            assert torch.equal(full[k], spread[k]), (k, kw["method"])
+        if kw["method"] == PLAIN:
+            plain = {k: v.cpu().numpy() for k, v in full.items()}
+        else:
+            assert int(full["counters"][2]) > 1000
+    o = oracle.render(oracle.Scene(prims), cam, light, med, method=oracle.METHOD_PLAIN_NEE, spp=1, seed=29)
+    frac, _ = compare_paths(plain, o, rel=LEARNED_REL)
+    assert frac < 4e-3 and o["events"].sum() > 100000
+
+
+@pytest.mark.parametrize("name", ["two", "many", "many_grid", "mesh"])
+@pytest.mark.parametrize("precision,kw", [(2, dict(flags=1)), (1, dict(nee_samples=16, nee_chain=3)),
+                                          (2, dict(nee_samples=5, nee_chain=1, flags=3, max_events=12))])
+def test_learned_steps_together_with_chains_and_fp8(msst, oracle, name, precision, kw):
+    """The learned paths above with FP8 decoders and with representative
+    events by chain length, in full waves and spread: bit for bit the same."""
+    announce(f"render learned together {name} precision={precision} {kw}")
+    packed = pack_all(msst, models_for_test(oracle)[1], precision)
+    r = together_scene(msst, name, 300, 240)
+    opts = dict(method=ST, sampler=CVAE, packed=packed, min_chain=0.0, tau_min=3.0, seed=7, chunk=1, spp=1, **kw)
+    med = dict(sigma_t=40.0, g=0.8, albedo=0.999)
+    full = r.render(med, blocks_per_cu=1, **opts)
+    spread = r.render(med, blocks_per_cu=64, **opts)
+    for k in full:
+        assert torch.equal(full[k], spread[k]), (k, int((full[k] != spread[k]).sum()))
+    assert int(full["counters"][2]) > 100
