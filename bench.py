@@ -97,7 +97,7 @@ def parse(argv=None):
     ap.add_argument("--no-focus", action="store_true")
     ap.add_argument("--no-density", action="store_true")
     ap.add_argument("--jsonl", type=str, default=None,
-                    help="also append the result line to this file (one JSON object per run)")
+                    help="also append the whole result, details included, to this file (one JSON object per run)")
     ap.add_argument("--no-confirm", action="store_true", help="skip the plain tracer's run at the matched spp")
     ap.add_argument("--no-walk-full", action="store_true")
     ap.add_argument("--no-sample", action="store_true")
@@ -634,6 +634,35 @@ def cpu_baseline(oracle, W, args, models):
                       f"trained FP32 masters and standardisation constants the GPU renders, tau_min "
                       f"{args.tau_min}, {args.nee_samples} representative events; {t_all:.1f} s on {threads} "
                       f"threads; single thread {paths1} paths in {t_one:.1f} s"}
+
+
+# What the printed line keeps of a section of measurements, what it leaves out
+# whole, and what it takes whole.
+HEADLINE_LEAVES = {
+    "absorption", "events_per_s", "mean_bias", "ms", "paths_per_s", "pt_ms", "pt_paths_per_s", "samples_per_s",
+    "sigma_t", "speedup_matched_rmse", "speedup_matched_rmse_oracle", "st_mean_bias", "st_ms", "st_paths_per_s",
+    "step_us_three_models_concurrent",
+}
+HEADLINE_OMIT = {"diagnostics", "event_long", "media", "regions", "table1_sweep"}
+HEADLINE_WHOLE = {"config", "cpu_baseline", "roofline", "walk"}
+
+
+def headline(result):
+    """The result in one line short enough (6 kB) for whoever keeps only the
+    end of a log; whole, with its per-region counts, errors and anchor
+    statistics, it is 23 kB.  The top-level figures and HEADLINE_WHOLE are as
+    they are, of the other sections there are the times, rates, biases and
+    speed-ups, to four digits."""
+    def part(v):
+        if isinstance(v, dict):
+            kept = {k: part(x) for k, x in v.items()
+                    if k not in HEADLINE_OMIT and (isinstance(x, (dict, list)) or k in HEADLINE_LEAVES)}
+            return {k: x for k, x in kept.items() if x not in ({}, [])}
+        if isinstance(v, list):
+            return [x for x in map(part, v) if isinstance(x, dict) and x]
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+    return {k: v if k in HEADLINE_WHOLE or not isinstance(v, (dict, list)) else part(v)
+            for k, v in result.items() if k not in HEADLINE_OMIT and (v is not None or k == "vs_baseline")}
 
 
 def main():
@@ -1209,11 +1238,10 @@ def main():
         "diagnostics": diag,
         "wall_s_timed": wall,
     }
-    line = json.dumps(result)
-    print(line, flush=True)
+    print(json.dumps(headline(result)), flush=True)
     if args.jsonl:
         with open(args.jsonl, "a") as fh:
-            fh.write(line + "\n")
+            fh.write(json.dumps(result) + "\n")
 
 
 if __name__ == "__main__":

@@ -1,6 +1,7 @@
 """Host-side pieces of bench.py that run without a GPU: argument defaults,
 the refusal of several GPUs, the measured-traffic reader and the image
 moments helper."""
+import json
 import os
 import subprocess
 import sys
@@ -165,3 +166,39 @@ def test_region_counts_average_per_pixel_means():
     assert set(r) == {"sphere", "box_arm"}
     assert r["sphere"]["pixels"] == 2 and r["sphere"]["events_per_path"] == 3.0 and r["sphere"]["steps_per_path"] == 0.5
     assert r["box_arm"]["events_per_path"] == 4.0 and r["box_arm"]["events_max"] == 10.0
+
+
+def test_printed_line_fits_the_end_of_a_log():
+    """The printed line holds the top-level figures exactly, the sections'
+    speed-ups and rates, and fits the 8000 characters that a log's reader may
+    keep, for a result of every section with its details."""
+    pair = dict(ms=5.68443152904510, rmse_st=0.005829128008843814, speedup_matched_rmse=0.9900513260089423, mean_st=0.0153178)
+    region = {r: dict(pixels=19655, events_per_path=106.18761, events_p99=160.1796875, events_max=204.75, steps_per_path=1.5)
+              for r in ("sphere", "box_arm")}
+    row = dict(sigma_t=1280.0, pt_ms=65.9432701110839, st_ms=8.6805979251, rmse_pt=0.0099112769, st_mean_bias=-0.0256820661,
+               speedup_matched_rmse=5.649969716596173, regions=dict(pt=region, st=region), event_long=dict(pair))
+    sig = dict(pair, pt_confirm=dict(pair, spp=256), st_paths_per_s=11685523334.43, pt_paths_per_s=11874833490.67,
+               mean_bias=8.812977411776224e-05,
+               oracle_anchor={f"stat{i}": 0.123456789012345 for i in range(14)} | {"speedup_matched_rmse_oracle": 0.98783499})
+    sections = {k: {s: dict(pair, mean_bias=1.234e-4) for s in ("10.0", "20.0", "40.0", "80.0")}
+                for k in ("table1", "other_step_form", "focus_training")}
+    result = dict(metric="paths/s", value=4798146722.994746, unit="paths/s", n_gpus=1, steps=20, warmup=5,
+                  ms_per_step=55.94565391540528, higher_is_better=True, scaling="weak", vs_baseline=None, dtype="f32+bf16",
+                  data="synthetic", config=dict(workload="w" * 300, paths_per_step=1 << 28), plain_paths_per_s=5989803115.818295,
+                  speedup_matched_rmse=0.9650981104025612, per_sigma={s: sig for s in ("10.0", "20.0", "40.0", "80.0")},
+                  walk=dict(photons=1 << 22, workload="w" * 100), roofline=dict(bound="alu", frac=0.5658972072638244),
+                  cpu_baseline=dict(value=8086058.154779512, sample="s" * 320), **sections,
+                  cvae_sample={f"model{m}_{p}": dict(samples_per_s=6.8042128641431e10, valu_frac=0.8894260183129774)
+                               for m in range(3) for p in ("bf16", "fp8")},
+                  density_sweep=dict(workload="w" * 200, rows=[row] * 5), absorption_sweep=[dict(row, absorption=0.0064)] * 6,
+                  c5={k: dict(pair, paths_per_s=4.64e8) for k in ("pt", "st_bf16", "st_fp8")}, rgb=dict(row, media=[pair] * 3),
+                  mesh={"40.0": row, "80.0": row}, table1_sweep=[pair] * 54, diagnostics=None)
+    line = json.dumps(bench.headline(result))
+    assert len(json.dumps(result)) > 16000 and len(line) < 7500
+    back = json.loads(line)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+              "dtype", "data", "config", "plain_paths_per_s", "speedup_matched_rmse", "walk", "roofline", "cpu_baseline"):
+        assert back[k] == result[k], k
+    assert back["density_sweep"]["rows"][4]["speedup_matched_rmse"] == 5.65
+    assert back["per_sigma"]["80.0"]["oracle_anchor"] == {"speedup_matched_rmse_oracle": 0.9878}
+    assert back["table1"]["40.0"]["ms"] == 5.684 and back["cvae_sample"]["model2_fp8"]["samples_per_s"] == 6.804e10
