@@ -232,10 +232,6 @@ __device__ __forceinline__ float tri_distance32(const float* t, V3 p, float& sha
     return d2;
 }
 
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
 __global__ __launch_bounds__(kGridThreads) void sdf_grid_mesh_kernel(const float* __restrict__ tris, int n_tris,
                                                                      int res, double lox, double loy, double loz,
                                                                      double hx, double hy, double hz, uint16_t* out) {

@@ -46,11 +46,6 @@ __device__ __forceinline__ const uint32_t* frag_tile(const PackedModel* pm, int 
 }
 static_assert(sizeof(PackedModel) % 16 == 0, "PackedModel must stay 16-byte sized");
 
-__device__ __forceinline__ bf16x4 load_frag_bf16(const PackedModel* pm, int layer) {
-    const uint2 u = *reinterpret_cast<const uint2*>(pm->frag[layer][lane_id()]);
-    return __builtin_bit_cast(bf16x4, u);
-}
-
 // FP8 E4M3 products on v_mfma_f32_16x16x32_fp8_fp8.  The contraction index
 // is permuted so that no data moves between layers: lane group q (lanes
 // 16q .. 16q+15) feeds K slots 8q .. 8q+3 with the four D rows 4q .. 4q+3 it

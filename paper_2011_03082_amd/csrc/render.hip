@@ -55,7 +55,7 @@ struct RenderArgs {
     int n_prims;
     const BvhNode* bvh;  // mesh scenes: nodes and reordered triangles
     const float* tris;
-    int n_nodes, n_tris;
+    int n_nodes;
     const uint16_t* grid;
     int res;
     float grid_lo[3], grid_inv_h[3], grid_half_diag;
@@ -65,7 +65,6 @@ struct RenderArgs {
     float light[3], intensity;
     float sigma_t, inv_sigma_t, g, albedo, ln_albedo;
     uint32_t surv_thr;
-    int method, sampler;
     const PackedModel* pm[3];
     float tau_min, r_cap, min_chain;  // r_cap = st_max / sigma_t
     Hg hg;
@@ -1894,10 +1893,6 @@ __global__ void sdf_grid_kernel(const float* prims, int n_prims, int res, double
     }
 }
 
-// Samples per work unit: small units balance the end of the persistent
-// kernel (a lane's last unit is its tail), large ones bound the partial
-// buffers.  About 2^24 units (64 per resident lane of a 256-CU device at
-// four 256-thread blocks per CU), and at least 2 samples per unit.
 // One render_kernel instance per (mode, geometry policy, radius source).
 template <int NP, bool GRID>
 static void launch_render(int mode, dim3 grid, dim3 block, hipStream_t hs, const RenderArgs& A) {
@@ -2002,7 +1997,6 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     A.bvh = mesh ? reinterpret_cast<const BvhNode*>(scene->bvh) : nullptr;
     A.tris = mesh ? scene->tris : nullptr;
     A.n_nodes = mesh ? scene->n_nodes : 0;
-    A.n_tris = mesh ? scene->n_tris : 0;
     A.grid = scene->sdf_fp16;
     A.res = scene->res;
     for (int k = 0; k < 3; ++k) {
@@ -2041,8 +2035,6 @@ ms_status sphere_trace_render(const ms_scene* scene, const ms_camera* cam, const
     A.albedo = medium->albedo;
     A.ln_albedo = (float)log((double)medium->albedo);
     A.surv_thr = (uint32_t)floor((double)medium->albedo * 16777216.0);
-    A.method = desc->method;
-    A.sampler = desc->sampler;
     for (int m = 0; m < 3; ++m) A.pm[m] = reinterpret_cast<const PackedModel*>(desc->packed[m]);
     A.tau_min = desc->tau_min;
     A.r_cap = desc->st_max * A.inv_sigma_t;
