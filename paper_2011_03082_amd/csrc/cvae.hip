@@ -1017,9 +1017,9 @@ struct SampleLds {
 // they are used leave registers for a fifth wave), matrix instructions on
 // vector registers (the attribute of the kernel: without it every tile moves
 // 24 values to and from accumulators), and values converted in pairs.  2^24
-// EventGen samples 557 -> 361 us in BF16, 578 -> 414 in FP8 (moving their 52
-// bytes a row takes 173), of Table 1's widest 1764 -> 870; 1000 samples 9.2 ->
-// 6.8 us.
+// EventGen samples 557 -> 338 us in BF16, 579 -> 403 in FP8 (moving their 52
+// bytes a row takes 173), of Table 1's widest 1769 -> 863; 1000 samples 8.7 ->
+// 6.2 us.
 template <int T>
 __device__ __forceinline__ void sample_rows(const PackedModel* pm, const float* cond, int64_t n, uint64_t seed,
                                             uint64_t id_offset, float* out, SampleLds<T>& L) {
@@ -1485,7 +1485,7 @@ ms_status cvae_sample(const void* packed_dev, const float* cond_dev, int64_t n, 
     if (st != MS_OK) return st;
     int64_t blocks = (n + 64 * kSampleWaves - 1) / (64 * kSampleWaves);
     // five blocks fit a CU; shares of a sixth of that even out the end (2^24
-    // samples 380 us with 8 blocks per CU, 367 with 20, 361 with 32 and with 64)
+    // samples 349 us with 8 blocks per CU, 336 to 338 with 20, 32 and 64)
     if (blocks > cus * 32) blocks = cus * 32;
     const PackedModel* pm = reinterpret_cast<const PackedModel*>(packed_dev);
     hipLaunchKernelGGL(cvae_sample_kernel, dim3((unsigned)blocks), dim3(64 * kSampleWaves), 0, (hipStream_t)stream, pm,

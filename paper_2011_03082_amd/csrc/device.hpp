@@ -18,7 +18,8 @@ namespace msst {
 // needs of them (s0, s1, s2) in place of the id, and a block takes 18 of the
 // 20 products.  A round's two exclusive ors are one v_bitop3_b32 each.  The
 // walk and the render loops are bound by VALU issue, and a 32 x 32 -> 64-bit
-// product issues at the full rate, so instructions are what counts: with the
+// product issues like a fused multiply-add (4.7 to 5 cycles of 2.4 GHz a wave
+// measured, transcendentals 9.7), so instructions are what counts: with the
 // shorter uniform and logarithm below, 2^22 training walks 117 -> 105 ms, the
 // 512^2 x 256 spp sphere and box image 15.4 -> 14.9 ms (plain, sigma_t 40) and
 // 16.0 -> 15.0 ms (learned, sigma_t 80).
@@ -82,9 +83,11 @@ __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sq
 __device__ __forceinline__ float fast_div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 
 // Natural log for free-flight lengths -log(u) / sigma_t, about 1 ulp: the
-// hardware log2 times ln 2 in two parts.  Same value as logf for every
-// uniform u in [2^-24, 1], without its scaling of denormals and its test for
-// infinities.
+// hardware log2 times ln 2 in two parts, the product's rounding taken up by
+// fused steps.  Constants and order are those into which LLVM's AMDGPU back end
+// expands logf, so that the value is logf's for every uniform u in [2^-24, 1]
+// (compared for all of them), without its scaling of denormals and its test
+// for infinities.
 __device__ __forceinline__ float flight_ln(float u) {
     const float y = __builtin_amdgcn_logf(u), hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
     const float r = y * hi;

@@ -17,7 +17,8 @@ namespace {
 // Splits are binned surface-area costs over all three axes in one pass, on
 // triangle bounds and centroids worked out once: a bin's bounds are folded from
 // both ends instead of anew for each split, and a split that moves no triangle
-// is not priced again (20 480 triangles on one core 11.7 -> 3.5 ms).  A minimum
+// is not priced again (20 480 triangles on one core 11.7 -> 3.5 ms, for 75
+// bytes of host memory a triangle beside the nodes instead of 4).  A minimum
 // keeps the earlier of equal values and skips NaN, in the order of the
 // triangles, so that a node's bytes, signs of zeros included, depend on the
 // triangles alone.
@@ -176,9 +177,9 @@ struct Builder {
 // neither depends on the order: the grid is the same bit for bit.
 //
 // VALU-bound, half on reading the triangles once and a quarter per brick and
-// half on the per-voxel filters.  20 480 triangles: 128^3 voxels 153 -> 5.9 ms,
-// 97^3 72 -> 3.0 ms; 1 280 triangles on 33^3 0.82 -> 0.13 ms; never slower down
-// to one triangle on 9^3.  Bricks of 8^3 read the triangles less often, but
+// half on the per-voxel filters.  20 480 triangles: 128^3 voxels 153 -> 5.4
+// ms, 97^3 72 -> 2.8 ms; 1 280 triangles on 33^3 0.82 -> 0.09 ms; never slower
+// down to one triangle on 9^3.  Bricks of 8^3 read the triangles less often, but
 // their lists overflow near the medial axis (the centre of a round body keeps
 // nearly every triangle): 15.8 ms.
 constexpr int kGridWaves = 8, kGridThreads = 64 * kGridWaves;

@@ -90,7 +90,7 @@ struct RenderArgs {
 // constants of the phase function, kept in registers -- and with the camera
 // every interval test's share of it, computed ahead of the loop -- pushed others
 // out of the 100 scalar and, at four waves per SIMD, 128 vector registers: the
-// learned C4 image 15.6 -> 14.6 ms (no vector spills are left, and 63 instead
+// learned C4 image 15.6 -> 14.6 ms (no vector spills are left, and 69 instead
 // of 118 scalar ones), the plain one 13.8 -> 13.3 ms.
 typedef const __attribute__((address_space(4))) RenderArgs* ColdArgs;
 __device__ __forceinline__ ColdArgs cold_args() {
@@ -395,7 +395,7 @@ struct GeoMany {
     // dirs[at]: each ray is given 64 / (rays) lanes, which share the primitives.
     // (Only flights longer than the radius at their start need it, a fifth to
     // a third of a wave's; on one lane each they took the wave through all
-    // primitives: 512^2 x 32 of 64 spheres 54.0 ms, 41.4 so and with the slots
+    // primitives: 512^2 x 64 of 64 spheres 54.0 ms, 41.4 so and with the slots
     // above.)
     __device__ __forceinline__ bool wave_piece(float4* from, float* index, const float4* dirs, bool need, V3 o, int at,
                                                float t, float& s, float& e) const {
@@ -551,7 +551,7 @@ struct GeoMany {
     // The same for the lanes in `active` of a converged wave, with the wave's
     // mask.  Up to 32 shadow rays have 2, up to 16 have 4 and up to 8 have 8
     // lanes each, which share the primitives; the first of them takes the
-    // others' hits over (more lanes hand over more than they save).  512^2 x 32
+    // others' hits over (more lanes hand over more than they save).  512^2 x 64
     // of 64 spheres 41.1 -> 38.6 ms; with the shared loop for full waves too
     // 44.9.
     __device__ __forceinline__ float wave_light(const RenderArgs& A, bool active, V3 x, V3 d, const uint64_t* mask) const {
@@ -1743,7 +1743,9 @@ __device__ __forceinline__ void render_loop(const RenderArgs& A, RenderLds& L, c
 }
 
 // Four waves per SIMD: measured faster than the unconstrained allocation
-// (three waves) despite a few spilled registers.
+// (three waves), also where it spills vector registers: 47 and 36 of the
+// learned kernels of many primitives, 30 of the meshes', 2 or fewer of three
+// or four primitives and of the plain kernels of many, none of the others.
 template <int MODE, int NP, bool GRID>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(const RenderArgs A) {
     // a wave's decoder rows (learned steps) or, between them, the paths that it

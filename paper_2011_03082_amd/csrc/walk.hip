@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void walk_kernel(const WalkArgs a) {
     // same state, reading the draws from LDS.  One wave issues an instruction
     // every 6 cycles: an event took 0.43 us alone and takes 0.11 (about 38
     // instructions, nearly all of them the turn of the direction); 2^22
-    // training walks 105 -> 56 ms, 2^16 73 -> 14 ms.
+    // training walks 105 -> 54 to 68 ms by seed and run, 2^16 73 -> 25 ms.
     auto walk_together = [&]() __attribute__((always_inline)) {
         WalkLds& L = lds_all[threadIdx.x >> 6];
         const int lane = lane_id();
@@ -570,12 +570,13 @@ ms_status ms_random_walk(const ms_walk_desc* desc, const ms_walk_out* out, void*
     a.ticket = reinterpret_cast<unsigned long long*>(workspace_dev);
 
     // Three blocks (as many as fit) keep VALU issue busy: 2^24 training walks
-    // in 120 / 104 / 104 ms with two / three / four, 2^22 in 59 / 56 / 59 ms; the
-    // end of a launch no longer depends on how many waves share a SIMD.
+    // in 119 / 101 / 114 ms with two / three / four.  At 2^22 the end of the
+    // launch is half of it, and 54 to 71 ms are measured with one to eight, as
+    // much by run and seed as by the number of blocks.
     const int bpc = d.blocks_per_cu ? d.blocks_per_cu : 3;
     // A few photons with long chains are spread over all waves: the fewer
     // chains a wave has, the sooner they walk together (2^16 training walks
-    // 29 -> 14 ms, 4096 22 -> 10 ms).  Where even the longest chains are short
+    // 30 -> 25 ms, 4096 22 -> 9 ms).  Where even the longest chains are short
     // (the expected events of the thickest, most backward medium, as in
     // order_bucket, or the event and absorption limits) full waves finish
     // them sooner: 10^5 analog walks of 17 events 0.14 ms, spread 0.25 ms.
