@@ -20,31 +20,34 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# Algorithmic VALU work per unit in 32-bit lane-operation slots (one per
-# full-rate lane operation, four per quarter-rate one: transcendentals and
-# 32-bit integer multiplies), from the operation count of the method:
-#   plain collision: Philox block (10 rounds, 20 quarter-rate multiplies) 100,
-#     uniforms 8, flight log 5, HG sample with its reciprocal 16, azimuth
-#     sin/cos 8, orthonormal frame 16, rotation with rsq 22, position update
-#     and exit test 13 (= 188, the walk event) plus the shadow ray to the
-#     light (two primitive intervals ~100, exp and HG phase ~30, weight and
-#     accumulation ~30) and the new ray's intervals: ~350;
-#   learned step with one representative event: 7 Philox blocks ~700, 22
-#     normals by Box-Muller ~240, 96 Softplus (two quarter-rate
-#     transcendentals each) ~1150, standardisation, posterior noise and
-#     de-standardisation ~250, exit frames ~120, shadow ray ~140: ~2600; each
-#     further representative event adds its first-event block and an
-#     EventGen decode (4 Philox blocks ~400, 10 normals ~110, 32 Softplus
-#     ~380) and a shadow ray ~140: ~1000;
-#   path: camera ray (one Philox block, pinhole direction) ~120, primary
-#     intervals ~65, banking the sample ~15: ~200.
+# Algorithmic VALU work per unit in 32-bit lane-operation slots, from the
+# operation count of the method.  A slot is one lane of an instruction at the
+# rate of a fused multiply-add; a 32 x 32 -> 64-bit product measures the same
+# rate (4.7 to 5 cycles a wave) and counts one, a transcendental, square root or
+# reciprocal half of it (9.7 cycles) and counts two:
+#   plain collision: the walk event, which is a Philox block (10 rounds of two
+#     products and two three-input xors) 40, uniforms 9, survival test 2, flight
+#     log 7, HG sample with its reciprocal and root 21, azimuth sin/cos 4,
+#     rotation 33, position update and exit test 7 (= 123), plus the shadow
+#     ray to the light (direction and distance 12, two primitive intervals 65,
+#     union 20, HG phase 10, exp, weight and accumulation 8, = 115) and the new
+#     ray's intervals 65: ~300;
+#   learned step with one representative event: 7 Philox blocks 280, 22
+#     normals by Box-Muller 198, 96 Softplus of 9 (two transcendentals each)
+#     864, standardisation, posterior noise and de-standardisation ~250,
+#     exit frames ~120, shadow ray 115, conversions ~70: ~1900; each further
+#     representative event adds its first-event block and an EventGen decode
+#     (4 Philox blocks 160, 10 normals 90, 32 Softplus 288, the rest ~50) and a
+#     shadow ray 115: ~700;
+#   path: camera ray (one Philox block, pinhole direction) ~75, primary
+#     intervals 65, banking the sample ~15: ~155.
 # achieved / peak is the fraction of the chip's lane slots the method's work
 # would fill; the kernels' own counted slots (SQ_THREAD_CYCLES_VALU fit, see
 # profiles/) are reported beside it.
-ALG_PER_PATH = 200.0
-ALG_PER_EVENT = 350.0
-ALG_PER_STEP_ONE_EVENT = 2600.0
-ALG_PER_EXTRA_EVENT = 1000.0
+ALG_PER_PATH = 155.0
+ALG_PER_EVENT = 300.0
+ALG_PER_STEP_ONE_EVENT = 1900.0
+ALG_PER_EXTRA_EVENT = 700.0
 OPS_PER_PATH = 404.0         # counted: camera ray, primary intervals, banking the result
 OPS_PER_EVENT = 436.0        # counted: one plain collision
 OPS_PER_STEP = 5050.0        # counted: one learned step with one representative event
