@@ -52,7 +52,7 @@ OPS_PER_PATH = 404.0         # counted: camera ray, primary intervals, banking t
 OPS_PER_EVENT = 436.0        # counted: one plain collision
 OPS_PER_STEP = 5050.0        # counted: one learned step with one representative event
 MFMA_FLOP_PER_STEP = 2944.0  # real decoder MACs x 2 (LengthGen + PathGen + EventGen)
-OPS_PER_WALK_EVENT = 167.0   # counted: one walk event: Philox block, HG sample, scatter, flight, exit test
+OPS_PER_WALK_EVENT = 138.0   # counted in full waves: one walk event: Philox block, HG sample, scatter, flight, exit test
 PEAK_VALU_LANEOPS = 256 * 2.4e9 * 64   # 3.93e13 lane-op slots/s, non-packed FP32 VALU
 CALIB_ROWS = 8192  # training conditions that calibrate the FP8 activation scales
 PEAK_MFMA_BF16 = 2.5e15
